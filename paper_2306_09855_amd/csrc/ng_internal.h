@@ -151,7 +151,7 @@ hipError_t launch_set_entries(const TabEntry* d_entries, uint32_t n, hipStream_t
 // r + tbits <= 32 and tbits < 32; "wide" = the full u32 key, u32 tgt and u32
 // weight.  Buckets, sub-buckets and the ranges of pass B are laid out on the
 // device from the counts, so no value travels back to the host.
-constexpr uint32_t kMsdTile = 10240;      // records per tile of passes A and C, and of B with unpacked records
+constexpr uint32_t kMsdTile = 10240;      // records per tile of pass A, and of B and C with unpacked records
 constexpr uint32_t kMsdTileN = 16384;     // records per tile of B with packed (8-byte) records
 constexpr uint32_t kMsdMaxDigit = 9;      // widest digit
 constexpr uint32_t kMsdMaxKeyBits = 27;   // 3 x kMsdMaxDigit

@@ -36,26 +36,18 @@ constexpr int kMThreads = 512;
 constexpr int kCntThreads = 1024;
 constexpr int kMWaves = kMThreads / 64;
 constexpr int kMItems = (int)kMsdTile / kMThreads;   // tile of pass A and of unpacked records
-constexpr int kMItemsN = (int)kMsdTileN / kMThreads;  // tile of packed records (passes B and C)
+constexpr int kMItemsN = (int)kMsdTileN / kMThreads;  // tile of packed records (pass B)
 static_assert(kMThreads * kMItems == (int)kMsdTile, "tile of unpacked records");
 static_assert(kMThreads * kMItemsN == (int)kMsdTileN, "tile of packed records");
 constexpr int kMNB = 1 << kMsdMaxDigit;  // 512 digit values at most
 static_assert(kMThreads >= kMNB, "one thread per digit value");
 static_assert(kMWaves % 2 == 0, "wave counters come in pairs");
-constexpr int kMLdsBlocks = 512;
-// Pass C sorts its tiles with twice the waves of the scatter passes: it holds
-// only the packed records (its LDS leaves room for the wave counters of 16
-// waves), and with half the records per thread it fits 1024 threads.
-constexpr int kCThreads = 1024;
-constexpr int kCWaves = kCThreads / 64;
-static_assert(kCWaves % 2 == 0 && kCThreads >= kMNB, "pass C waves");
 
 // Per-wave digit counters in LDS: waves 2v and 2v + 1 share the words
 // wh[v][d], wave 2v in the low and wave 2v + 1 in the high 16 bits.  A
 // wave's count of one digit in a tile is at most 64 x 32 records, and a
 // tile position at most 16,384, so neither half carries into the other.
 constexpr int kMWhWords = kMWaves / 2 * kMNB;
-constexpr int kCWhWords = kCWaves / 2 * kMNB;
 __device__ __forceinline__ uint32_t wh_at(int wave, uint32_t d) { return (uint32_t)(wave >> 1) * kMNB + d; }
 __device__ __forceinline__ uint32_t wh_shift(int wave) { return (uint32_t)(wave & 1) * 16u; }
 __device__ __forceinline__ uint32_t wh_get(const uint32_t* wh, int wave, uint32_t d) {
@@ -67,7 +59,7 @@ enum { IN_BLOCKS = 0, IN_NARROW = 1, IN_WIDE = 2 };
 // Thread index as the shared helpers read it.  TidOpaque hides it from the
 // compiler at every use, so that values derived from it are recomputed where
 // they are needed instead of being computed once and held in registers for
-// the whole kernel: pass C's tile loop then fits 1,024 threads without
+// the whole kernel: pass C's tile loop then fits 128 registers without
 // spilling (its per-slot LDS and global offsets otherwise fill the register
 // file).  The scatter passes keep the plain index (faster there: 1.77 vs
 // 1.99 ms for pass A at 3e8).
@@ -758,25 +750,24 @@ __global__ __launch_bounds__(256) void k_msd_split(MsdPlan p) {
 // D3, and its sorted order is its final order, so the tile is written to
 // [sbstart[sb], sbstart[e]) as one contiguous run.  A sub-bucket larger than
 // one load is its own tile and is sorted in pieces after a counting pass.
-// Output block of a sorted position: from the LDS copy of the block table
-// when it holds all of them.
-__device__ __forceinline__ char* m_out_block(const MsdPlan& p, char* const* s_blk, uint32_t dest) {
-  return s_blk ? s_blk[dest >> p.log2B] : C(p.out_blocks, dest >> p.log2B);
-}
-
-// Records per LDS load of pass C: 10,240 for packed and unpacked records,
-// 10 per thread of 1,024.  (Measured on the 3e8 microcircuit, with 512
-// threads: 16,384-record tiles spill registers and took 2.46 ms; 6,144-record
-// tiles with two workgroups per CU need a narrower last digit, hence a 9-bit
-// second scatter, and took 2.38 ms plus 0.7 ms more in pass B; 10,240: 2.17
-// ms.  With 1,024 threads: 2.03 ms; stores through a scalar block base for
-// runs inside one block, next to the general store loop: 2.15 ms.)
+// Workgroup of pass C and the records it sorts in LDS at once.  Packed
+// records: 8,192 in 512 threads of at most 128 registers and 80 KB of LDS, so
+// that two workgroups share a CU and one ranks while the other reads and
+// writes (the pass is bound by latency and the vector units, not by its 22
+// bytes per record: 3e8 microcircuit 1.93 -> 1.65 ms, 3.4 -> 4.0 TB/s,
+// against 10,240 records in one workgroup of 1,024 threads; with that one,
+// 16,384-record tiles spill registers and took 2.46 ms).  Unpacked records (12
+// bytes) do not fit twice: one workgroup of 1,024 threads and 10,240 records.
 template <bool NARROW>
 struct CSize {
-  static constexpr int ITEMS = (int)kMsdTile / kCThreads;
-  static constexpr uint32_t TILE = (uint32_t)(ITEMS * kCThreads);
+  static constexpr int THREADS = NARROW ? 512 : 1024;
+  static constexpr int WAVES = THREADS / 64;
+  static constexpr int WAVES_PER_SIMD = 4;  // two workgroups of 8 waves, or one of 16
+  static constexpr uint32_t TILE = NARROW ? 8192 : kMsdTile;
+  static constexpr int ITEMS = (int)TILE / THREADS;
+  static constexpr int WH_WORDS = WAVES / 2 * kMNB;
+  static_assert(WAVES % 2 == 0 && THREADS >= kMNB, "pass C waves");
 };
-static_assert(CSize<true>::TILE == kMsdTile, "tile of pass C");
 constexpr uint32_t kCMaxSub = 63;      // sub-buckets per tile: lanes 1..63 test the ends
 
 // Sub-buckets per tile: bounded by the lanes of one wave, by 9-bit combined
@@ -884,13 +875,12 @@ __device__ __forceinline__ void tile_groups(const MsdPlan& p, uint32_t sba, uint
   __shared__ uint32_t s_k[CSize<NARROW>::TILE];              \
   __shared__ uint32_t s_t[NARROW ? 1 : CSize<NARROW>::TILE]; \
   __shared__ uint32_t s_w[CSize<NARROW>::TILE];              \
-  __shared__ uint32_t s_wh[kCWhWords];           \
+  __shared__ uint32_t s_wh[CSize<NARROW>::WH_WORDS]; \
   __shared__ uint32_t s_st[kMNB + 1];            \
   __shared__ uint32_t s_ex[kMNB + 1];            \
-  __shared__ uint32_t s_tmp[kCWaves];            \
+  __shared__ uint32_t s_tmp[CSize<NARROW>::WAVES];   \
   __shared__ uint32_t s_sink[64];                \
-  __shared__ uint32_t s_bal[kMNB / 32];          \
-  __shared__ char* s_blk_tab[kMLdsBlocks];
+  __shared__ uint32_t s_bal[kMNB / 32];
 
 // Key-field constants of pass C: a record holds the low cbits key bits above
 // its target (packed) or the whole key, so the combined digit of a tile is
@@ -914,35 +904,27 @@ __device__ __forceinline__ CFields c_fields(const MsdPlan& p) {
   return f;
 }
 
-// Block table in LDS when it fits; clears the per-wave digit counters.
-__device__ __forceinline__ char* const* c_setup(const MsdPlan& p, char** s_blk_tab, uint32_t* s_wh) {
-  const uint32_t n_out_blocks = (uint32_t)(((uint64_t)p.n + (1ull << p.log2B) - 1) >> p.log2B);
-  char* const* s_blk = n_out_blocks <= (uint32_t)kMLdsBlocks ? s_blk_tab : nullptr;
-  if (s_blk)
-    for (uint32_t b = TidOpaque::get(); b < n_out_blocks; b += kCThreads) s_blk_tab[b] = C(p.out_blocks, b);
-  for (uint32_t d = TidOpaque::get(); d < (uint32_t)kMNB; d += kCThreads) {
-#pragma unroll
-    for (int v = 0; v < kCWaves / 2; ++v) s_wh[v * kMNB + d] = 0;
-  }
-  return s_blk;
-}
-
 // Records staged in sorted order at [0, cnt) of the LDS arrays go out to
-// their positions: dest = dx[digit] + lp (or r0 + lp when dx is null).
+// their positions: dest = r0 + lp, a run over at most two blocks whose
+// addresses are read once, or dx[digit] + lp (dx not null: a large sub-bucket
+// in pieces), each record's block read from the table.
 template <bool NARROW>
-__device__ __forceinline__ void c_store(const MsdPlan& p, const CFields& f, char* const* s_blk, const uint32_t* s_k,
-                                        const uint32_t* s_t, const uint32_t* s_w, uint32_t cnt, uint32_t base,
-                                        uint32_t kb, const uint32_t* dx, uint32_t r0) {
+__device__ __forceinline__ void c_store(const MsdPlan& p, const CFields& f, const uint32_t* s_k, const uint32_t* s_t,
+                                        const uint32_t* s_w, uint32_t cnt, uint32_t base, uint32_t kb,
+                                        const uint32_t* dx, uint32_t r0) {
   const uint64_t B = 1ull << p.log2B;
+  const uint32_t bA = r0 >> p.log2B;
+  char* const blkA = dx ? nullptr : C(p.out_blocks, bA);
+  char* const blkZ = dx ? nullptr : C(p.out_blocks, (r0 + cnt - 1) >> p.log2B);
 #pragma unroll
   for (int k = 0; k < CSize<NARROW>::ITEMS; ++k) {
-    const uint32_t lp = (uint32_t)(k * kCThreads + TidOpaque::get());
+    const uint32_t lp = (uint32_t)(k * CSize<NARROW>::THREADS + TidOpaque::get());
     if (lp < cnt) {
       const uint32_t kk = s_k[lp];
       const uint32_t dg = ((kk >> f.ks) - base) & f.km;
       const uint32_t dest = dx ? dx[dg] + lp : r0 + lp;
       const uint32_t key = kb + dg;
-      char* blk = m_out_block(p, s_blk, dest);
+      char* blk = dx ? G(p.out_blocks)[dest >> p.log2B] : ((dest >> p.log2B) == bA ? blkA : blkZ);
       const uint64_t o = dest & (B - 1);
       G(reinterpret_cast<uint32_t*>(blk))[o] = key >> p.dbits;
       G(reinterpret_cast<uint32_t*>(blk + 4 * B))[o] = NARROW ? (kk & f.tmask) : s_t[lp];
@@ -971,10 +953,11 @@ __device__ __forceinline__ void c_stage(const CFields& f, const Recs<CSize<NARRO
   }
 }
 
+template <bool NARROW>
 __device__ __forceinline__ void clear_wh(uint32_t* s_wh) {
-  for (uint32_t e = TidOpaque::get(); e < (uint32_t)kMNB; e += kCThreads) {
+  for (uint32_t e = TidOpaque::get(); e < (uint32_t)kMNB; e += CSize<NARROW>::THREADS) {
 #pragma unroll
-    for (int v = 0; v < kCWaves / 2; ++v) s_wh[v * kMNB + e] = 0;
+    for (int v = 0; v < CSize<NARROW>::WAVES / 2; ++v) s_wh[v * kMNB + e] = 0;
   }
 }
 
@@ -982,12 +965,12 @@ __device__ __forceinline__ void clear_wh(uint32_t* s_wh) {
 // records of the next tile load while a tile is written.  Sub-buckets larger
 // than one load are listed for k_msd_big_c.
 template <int RB, bool NARROW>
-__global__ __launch_bounds__(kCThreads) void k_msd_tiles_c(MsdPlan p) {
+__global__ __launch_bounds__(CSize<NARROW>::THREADS, CSize<NARROW>::WAVES_PER_SIMD) void k_msd_tiles_c(MsdPlan p) {
   M_C_LDS
   __shared__ CTile s_next[2];  // by iteration parity: wave 0 writes one while the other is read
   const int lane = TidOpaque::get() & 63, wave = TidOpaque::get() >> 6;
   const CFields f = c_fields<NARROW>(p);
-  char* const* s_blk = c_setup(p, s_blk_tab, s_wh);
+  clear_wh<NARROW>(s_wh);
   const uint32_t b3 = p.b3;
   const uint32_t sb0 = p.wg_sb0[blockIdx.x], sb_end = p.wg_sb0[blockIdx.x + 1];
   if (wave == 0) {
@@ -1033,15 +1016,15 @@ __global__ __launch_bounds__(kCThreads) void k_msd_tiles_c(MsdPlan p) {
       lds_barrier();
       uint32_t st, ex, all;
       const uint32_t d = TidOpaque::get();
-      const uint32_t tot = digit_starts_present<kCWaves, TidOpaque>(nd, s_wh, s_tmp, &st, &ex, &all);
+      const uint32_t tot = digit_starts_present<CSize<NARROW>::WAVES, TidOpaque>(nd, s_wh, s_tmp, &st, &ex, &all);
       tile_groups(p, cur.sb, nsub, cur.r0, d < nd ? tot : 0u, st, ex, all & 1023u, s_ex, s_st, s_bal);
       c_stage<NARROW>(f, r, pos, n, base, s_wh, s_k, s_t, s_w);
       lds_barrier();
-      clear_wh(s_wh);
+      clear_wh<NARROW>(s_wh);
       const CTile nx = s_next[par];
       loaded = tile_fits<NARROW>(nx);
       if (loaded) load_c<NARROW>(f.ik, f.it, f.iw, nx.r0, nx.r1 - nx.r0, r);
-      c_store<NARROW>(p, f, s_blk, s_k, s_t, s_w, n, base, cur.sb << b3, nullptr, cur.r0);
+      c_store<NARROW>(p, f, s_k, s_t, s_w, n, base, cur.sb << b3, nullptr, cur.r0);
     }
     lds_barrier();  // s_next[par] is complete; the tile's LDS is free
     const CTile nx = s_next[par];
@@ -1058,28 +1041,28 @@ __global__ __launch_bounds__(kCThreads) void k_msd_tiles_c(MsdPlan p) {
 // pieces of one load, each piece's records of a D3 value following those of
 // the pieces before.
 template <int RB, bool NARROW>
-__global__ __launch_bounds__(kCThreads) void k_msd_big_c(MsdPlan p) {
+__global__ __launch_bounds__(CSize<NARROW>::THREADS) void k_msd_big_c(MsdPlan p) {
   M_C_LDS
   __shared__ uint32_t s_cur[kMNB];
   __shared__ uint32_t s_dx[kMNB];
   const CFields f = c_fields<NARROW>(p);
-  char* const* s_blk = c_setup(p, s_blk_tab, s_wh);
+  clear_wh<NARROW>(s_wh);
   const uint32_t b3 = p.b3, nd = 1u << b3, d = TidOpaque::get();
   lds_barrier();
   for (uint32_t i = blockIdx.x; i < G(p.big_count)[0]; i += gridDim.x) {
     const uint32_t sb = G(p.big_list)[i];
     const uint32_t r0 = G(p.sbstart)[sb], n = G(p.sbstart)[sb + 1] - r0;
     const uint32_t base = (sb << b3) & f.km;
-    for (uint32_t e = d; e < (uint32_t)kMNB; e += kCThreads) s_cur[e] = 0;
+    for (uint32_t e = d; e < (uint32_t)kMNB; e += CSize<NARROW>::THREADS) s_cur[e] = 0;
     lds_barrier();
-    for (uint32_t j = d; j < n; j += kCThreads) atomicAdd(&s_cur[((G(f.ik)[r0 + j] >> f.ks) - base) & f.km], 1u);
+    for (uint32_t j = d; j < n; j += CSize<NARROW>::THREADS) atomicAdd(&s_cur[((G(f.ik)[r0 + j] >> f.ks) - base) & f.km], 1u);
     lds_barrier();
     {
       // a large sub-bucket may hold any number of records per digit: two scans
       const uint32_t h = d < nd ? s_cur[d] : 0u;
       uint32_t all_rec, all_present;
-      const uint32_t hst = m_block_scan<kCWaves, TidOpaque>(h, s_tmp, &all_rec);
-      const uint32_t ex = m_block_scan<kCWaves, TidOpaque>(h ? 1u : 0u, s_tmp, &all_present);
+      const uint32_t hst = m_block_scan<CSize<NARROW>::WAVES, TidOpaque>(h, s_tmp, &all_rec);
+      const uint32_t ex = m_block_scan<CSize<NARROW>::WAVES, TidOpaque>(h ? 1u : 0u, s_tmp, &all_present);
       tile_groups(p, sb, 1u, r0, h, hst, ex, all_present, s_ex, s_st, s_bal);
       lds_barrier();
       if (d < nd) s_cur[d] = r0 + hst;
@@ -1092,7 +1075,7 @@ __global__ __launch_bounds__(kCThreads) void k_msd_big_c(MsdPlan p) {
       rank_digits<RB, CSize<NARROW>::ITEMS, false, TidOpaque>(r.k, f.ks, f.km, cnt, s_wh, s_sink, pos, base);
       lds_barrier();
       uint32_t st;
-      const uint32_t tot = digit_starts<kCWaves, TidOpaque>(nd, s_wh, s_tmp, &st);
+      const uint32_t tot = digit_starts<CSize<NARROW>::WAVES, TidOpaque>(nd, s_wh, s_tmp, &st);
       if (d < nd) {
         const uint32_t cp = s_cur[d];
         s_dx[d] = cp - st;  // output position minus piece position
@@ -1101,8 +1084,8 @@ __global__ __launch_bounds__(kCThreads) void k_msd_big_c(MsdPlan p) {
       lds_barrier();  // every digit's wave starts are in s_wh
       c_stage<NARROW>(f, r, pos, cnt, base, s_wh, s_k, s_t, s_w);
       lds_barrier();
-      clear_wh(s_wh);
-      c_store<NARROW>(p, f, s_blk, s_k, s_t, s_w, cnt, base, sb << b3, s_dx, 0u);
+      clear_wh<NARROW>(s_wh);
+      c_store<NARROW>(p, f, s_k, s_t, s_w, cnt, base, sb << b3, s_dx, 0u);
       lds_barrier();
     }
   }
@@ -1150,7 +1133,7 @@ inline int rb_class(uint32_t bits) { return bits <= 6 ? 6 : (bits <= 8 ? 8 : 9);
 
 }  // namespace
 
-uint32_t msd_cap(bool) { return kMsdTile; }
+uint32_t msd_cap(bool narrow) { return narrow ? CSize<true>::TILE : CSize<false>::TILE; }
 
 #define M_RB_SWITCH(bits, F) \
   switch (rb_class(bits)) {  \
@@ -1221,8 +1204,8 @@ static uint32_t c_digit_bits(const MsdPlan& p, bool narrow) {
 hipError_t launch_msd_tiles_c(const MsdPlan& p, hipStream_t s) {
   const bool narrow = p.b2 ? p.narrow_b : p.narrow_a;
 #define F(RB)                                                                                           \
-  if (narrow) hipLaunchKernelGGL((k_msd_tiles_c<RB, true>), dim3(p.wgs_c), dim3(kCThreads), 0, s, p);   \
-  else hipLaunchKernelGGL((k_msd_tiles_c<RB, false>), dim3(p.wgs_c), dim3(kCThreads), 0, s, p);
+  if (narrow) hipLaunchKernelGGL((k_msd_tiles_c<RB, true>), dim3(p.wgs_c), dim3(CSize<true>::THREADS), 0, s, p);   \
+  else hipLaunchKernelGGL((k_msd_tiles_c<RB, false>), dim3(p.wgs_c), dim3(CSize<false>::THREADS), 0, s, p);
   M_RB_SWITCH(c_digit_bits(p, narrow), F)
 #undef F
   return hipGetLastError();
@@ -1232,8 +1215,8 @@ hipError_t launch_msd_big_c(const MsdPlan& p, hipStream_t s) {
   const bool narrow = p.b2 ? p.narrow_b : p.narrow_a;
   const dim3 grid(p.max_big < 256u ? p.max_big : 256u);
 #define F(RB)                                                                                      \
-  if (narrow) hipLaunchKernelGGL((k_msd_big_c<RB, true>), grid, dim3(kCThreads), 0, s, p);          \
-  else hipLaunchKernelGGL((k_msd_big_c<RB, false>), grid, dim3(kCThreads), 0, s, p);
+  if (narrow) hipLaunchKernelGGL((k_msd_big_c<RB, true>), grid, dim3(CSize<true>::THREADS), 0, s, p);          \
+  else hipLaunchKernelGGL((k_msd_big_c<RB, false>), grid, dim3(CSize<false>::THREADS), 0, s, p);
   M_RB_SWITCH(p.b3, F)
 #undef F
   return hipGetLastError();
