@@ -402,10 +402,7 @@ __device__ __forceinline__ void sort_tile(const SortIO& io, uint64_t base, uint3
       }
 #pragma unroll
       for (int b = 0; b < RB; ++b) {
-        const uint32_t sb = (uint32_t)((int32_t)(dg << (31 - b)) >> 31);  // bit b, all ones or zero
-        const uint64_t m = __ballot(sb != 0u);
-        plo &= ~((uint32_t)m ^ sb);
-        phi &= ~((uint32_t)(m >> 32) ^ sb);
+        match_bit(dg, b, plo, phi);
       }
       const uint32_t below = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
       const uint32_t tot = (uint32_t)__popc(plo) + (uint32_t)__popc(phi);

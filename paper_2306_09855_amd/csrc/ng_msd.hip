@@ -205,10 +205,7 @@ __device__ __forceinline__ void rank_digits(const uint32_t (&key)[ITEMS], uint32
 #pragma unroll
       for (int b = 0; b < RB; ++b) {
         if ((uint32_t)b < nbits) {  // digits are below 2^nbits (a uniform test)
-          const uint32_t sb = (uint32_t)((int32_t)(d << (31 - b)) >> 31);  // bit b, all ones or zero
-          const uint64_t m = __ballot(sb != 0u);
-          plo &= ~((uint32_t)m ^ sb);
-          phi &= ~((uint32_t)(m >> 32) ^ sb);
+          match_bit(d, b, plo, phi);
         }
       }
       const uint32_t below = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
