@@ -153,6 +153,7 @@ hipError_t launch_set_entries(const TabEntry* d_entries, uint32_t n, hipStream_t
 // device from the counts, so no value travels back to the host.
 constexpr uint32_t kMsdTile = 10240;      // records per tile of pass A, and of B and C with unpacked records
 constexpr uint32_t kMsdTileN = 16384;     // records per tile of B with packed (8-byte) records
+constexpr uint32_t kMsdBigPiece = 65536;   // records per piece of a sub-bucket larger than one LDS load
 constexpr uint32_t kMsdMaxDigit = 9;      // widest digit
 constexpr uint32_t kMsdMaxKeyBits = 27;   // 3 x kMsdMaxDigit
 
@@ -182,8 +183,11 @@ struct MsdPlan {
   uint32_t* tprb;                   // [2^b1] tiles per range of pass B of each bucket
   uint32_t* sbstart;                // [2^(b1+b2) + 1] sub-bucket starts
   uint32_t* wg_sb0;                 // [wgs_c + 1] first sub-bucket of each workgroup of C
-  uint32_t* big_count;              // sub-buckets larger than one LDS load (set by pass C)
-  uint32_t* big_list;               // [max_big] their numbers
+  uint32_t* big_count;              // [2] sub-buckets larger than one LDS load, their pieces (set by pass C)
+  uint2* big_list;                  // [max_big] (sub-bucket, its first piece)
+  uint32_t* big_piece;              // [max_pieces] the list entry of each piece of kMsdBigPiece records
+  uint32_t* cnt_big;                // [max_pieces << b3] D3 counts of the pieces, then their first positions
+  uint32_t max_pieces;              // n / kMsdBigPiece + max_big
   uint32_t max_big;                 // n / (one load + 1) + 1
   uint32_t* gcount;                 // [2^(b1+b2) + 1] groups per sub-bucket, scanned in place
   uint32_t* gmask;                  // [2^(b1+b2) * mask_words] present D3 values per sub-bucket
@@ -204,7 +208,8 @@ hipError_t launch_msd_plan_b(const MsdPlan& p, hipStream_t s);
 hipError_t launch_msd_count_b(const MsdPlan& p, hipStream_t s);
 hipError_t launch_msd_scatter_b(const MsdPlan& p, hipStream_t s);
 hipError_t launch_msd_plan_c(const MsdPlan& p, hipStream_t s);
-// pass C: tiles of whole sub-buckets, then the sub-buckets larger than one load
+// pass C: tiles of whole sub-buckets, then the sub-buckets larger than one
+// load (count, scan, scatter)
 hipError_t launch_msd_tiles_c(const MsdPlan& p, hipStream_t s);
 hipError_t launch_msd_big_c(const MsdPlan& p, hipStream_t s);
 hipError_t launch_msd_groups(const MsdPlan& p, hipStream_t s);

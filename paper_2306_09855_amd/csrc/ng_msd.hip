@@ -722,7 +722,7 @@ __global__ __launch_bounds__(256) void k_msd_zero(MsdPlan p) {
 __global__ __launch_bounds__(256) void k_msd_split(MsdPlan p) {
   const uint32_t nsb = 1u << (p.b1 + p.b2);
   const uint32_t w = blockIdx.x * 256u + threadIdx.x;
-  if (w == 0) *p.big_count = 0;  // sub-buckets listed by pass C
+  if (w < 2) p.big_count[w] = 0;  // sub-buckets and pieces listed by pass C
   if (w > p.wgs_c) return;
   // the last boundary is the first sub-bucket past the records: the empty
   // sub-buckets above it are never visited (their group counts and masks are
@@ -960,7 +960,7 @@ __device__ __forceinline__ void clear_wh(uint32_t* s_wh) {
 
 // Tiles of the workgroup's sub-buckets [wg_sb0[w], wg_sb0[w + 1]); the
 // records of the next tile load while a tile is written.  Sub-buckets larger
-// than one load are listed for k_msd_big_c.
+// than one load are listed for the k_msd_big_* kernels.
 template <int RB, bool NARROW>
 __global__ __launch_bounds__(CSize<NARROW>::THREADS, CSize<NARROW>::WAVES_PER_SIMD) void k_msd_tiles_c(MsdPlan p) {
   M_C_LDS
@@ -993,8 +993,13 @@ __global__ __launch_bounds__(CSize<NARROW>::THREADS, CSize<NARROW>::WAVES_PER_SI
     if (wave == 0) probe = tile_probe(p, cur.e, lim);  // used after the ranking
     if (n == 0 || n > TILE) {
       // empty sub-buckets: nothing to do; one sub-bucket too large for one
-      // load: listed for k_msd_big_c
-      if (n && TidOpaque::get() == 0) G(p.big_list)[atomicAdd(p.big_count, 1u)] = cur.sb;
+      // load: listed, with its pieces, for the k_msd_big_* kernels
+      if (n && TidOpaque::get() == 0) {
+        const uint32_t np = (n + kMsdBigPiece - 1) / kMsdBigPiece;
+        const uint32_t slot = atomicAdd(p.big_count, 1u), p0 = atomicAdd(p.big_count + 1, np);
+        st_u32x2(p.big_list + slot, cur.sb, p0);
+        for (uint32_t j = 0; j < np; ++j) G(p.big_piece)[p0 + j] = slot;
+      }
       if (wave == 0) {
         const CTile t = tile_finish(probe, cur.e, lim, f.msub, TILE);
         if (lane == 0) s_next[par] = t;
@@ -1034,40 +1039,104 @@ __global__ __launch_bounds__(CSize<NARROW>::THREADS, CSize<NARROW>::WAVES_PER_SI
   }
 }
 
-// The listed sub-buckets larger than one load: counted by D3, then sorted in
-// pieces of one load, each piece's records of a D3 value following those of
-// the pieces before.
+// The listed sub-buckets larger than one load (sources with very many
+// connections), in pieces of kMsdBigPiece records spread over the chip:
+// k_msd_big_count counts each piece's D3 values, k_msd_big_scan turns a
+// sub-bucket's counts into every piece's first output position per D3 value
+// and records its groups, and k_msd_big_scatter sorts each piece, one load
+// after another, to those positions.  (One workgroup per sub-bucket took 5.3
+// ms of the 4,096-call batch, whose calls draw from as little as one source;
+// in pieces: see launch_msd_big_c.)
+struct BigPiece {
+  uint32_t sb, lo, hi;  // records [lo, hi) of sub-bucket sb
+};
+__device__ __forceinline__ BigPiece big_piece(const MsdPlan& p, uint32_t i) {
+  const u32x2 e = *(const NG_GLOBAL u32x2*)(p.big_list + G(p.big_piece)[i]);  // (sub-bucket, first piece)
+  BigPiece q;
+  q.sb = e.x;
+  const uint32_t end = G(p.sbstart)[q.sb + 1];
+  q.lo = G(p.sbstart)[q.sb] + (i - e.y) * kMsdBigPiece;
+  q.hi = end - q.lo < kMsdBigPiece ? end : q.lo + kMsdBigPiece;
+  return q;
+}
+
+template <bool NARROW>
+__global__ __launch_bounds__(kCntThreads) void k_msd_big_count(MsdPlan p) {
+  __shared__ uint32_t hist[kMNB];
+  const CFields f = c_fields<NARROW>(p);
+  const uint32_t nd = 1u << p.b3, m = nd - 1, n_pieces = G(p.big_count)[1];
+  for (uint32_t i = blockIdx.x; i < n_pieces; i += gridDim.x) {
+    for (uint32_t d = threadIdx.x; d < nd; d += kCntThreads) hist[d] = 0;
+    __syncthreads();
+    const BigPiece q = big_piece(p, i);
+    // 16-byte loads over the aligned middle, single words at the ends
+    const uint32_t a0 = min(q.hi, (q.lo + 3u) & ~3u), a1 = max(a0, q.hi & ~3u);
+    if (q.lo + threadIdx.x < a0) atomicAdd(&hist[(G(f.ik)[q.lo + threadIdx.x] >> f.ks) & m], 1u);
+    if (a1 + threadIdx.x < q.hi) atomicAdd(&hist[(G(f.ik)[a1 + threadIdx.x] >> f.ks) & m], 1u);
+    const NG_GLOBAL u32x4* v = (const NG_GLOBAL u32x4*)(f.ik + a0);
+    const uint32_t nq = (a1 - a0) / 4;
+    for (uint32_t j = threadIdx.x; j < nq; j += kCntThreads) {
+      const u32x4 x = v[j];
+      hist_add4(hist, (x.x >> f.ks) & m, (x.y >> f.ks) & m, (x.z >> f.ks) & m, (x.w >> f.ks) & m);
+    }
+    __syncthreads();
+    for (uint32_t d = threadIdx.x; d < nd; d += kCntThreads) p.cnt_big[((uint64_t)i << p.b3) + d] = hist[d];
+  }
+}
+
+__global__ __launch_bounds__(kMThreads) void k_msd_big_scan(MsdPlan p) {
+  __shared__ uint32_t s_st[kMNB + 1], s_ex[kMNB + 1], s_tmp[kMWaves], s_bal[kMNB / 32];
+  const uint32_t nd = 1u << p.b3, d = threadIdx.x, n_big = G(p.big_count)[0];
+  for (uint32_t i = blockIdx.x; i < n_big; i += gridDim.x) {
+    const u32x2 e = *(const NG_GLOBAL u32x2*)(p.big_list + i);
+    const uint32_t r0 = G(p.sbstart)[e.x], n = G(p.sbstart)[e.x + 1] - r0;
+    const uint32_t np = (n + kMsdBigPiece - 1) / kMsdBigPiece;
+    NG_GLOBAL uint32_t* cnt = G(p.cnt_big) + ((uint64_t)e.y << p.b3) + d;  // thread d: its D3 value's counts
+    uint32_t h = 0;
+    if (d < nd) {
+#pragma unroll 8
+      for (uint32_t j = 0; j < np; ++j) h += cnt[(uint64_t)j << p.b3];
+    }
+    // a large sub-bucket may hold any number of records per digit: two scans
+    uint32_t all_rec, all_present;
+    const uint32_t hst = m_block_scan(h, s_tmp, &all_rec);
+    const uint32_t ex = m_block_scan(h ? 1u : 0u, s_tmp, &all_present);
+    tile_groups(p, e.x, 1u, r0, h, hst, ex, all_present, s_ex, s_st, s_bal);
+    if (d < nd) {
+      uint32_t at = r0 + hst;
+#pragma unroll 8
+      for (uint32_t j = 0; j < np; ++j) {
+        const uint32_t c = cnt[(uint64_t)j << p.b3];
+        cnt[(uint64_t)j << p.b3] = at;
+        at += c;
+      }
+    }
+    lds_barrier();  // the LDS is reused by the next sub-bucket
+  }
+}
+
 template <int RB, bool NARROW>
-__global__ __launch_bounds__(CSize<NARROW>::THREADS) void k_msd_big_c(MsdPlan p) {
-  M_C_LDS
-  __shared__ uint32_t s_cur[kMNB];
-  __shared__ uint32_t s_dx[kMNB];
+__global__ __launch_bounds__(CSize<NARROW>::THREADS, CSize<NARROW>::WAVES_PER_SIMD) void k_msd_big_scatter(MsdPlan p) {
+  __shared__ uint32_t s_k[CSize<NARROW>::TILE];
+  __shared__ uint32_t s_t[NARROW ? 1 : CSize<NARROW>::TILE];
+  __shared__ uint32_t s_w[CSize<NARROW>::TILE];
+  __shared__ uint32_t s_wh[CSize<NARROW>::WH_WORDS];
+  __shared__ uint32_t s_tmp[CSize<NARROW>::WAVES];
+  __shared__ uint32_t s_sink[64];
+  __shared__ uint32_t s_cur[kMNB];  // next output position per digit
+  __shared__ uint32_t s_dx[kMNB];   // output position minus tile position
   const CFields f = c_fields<NARROW>(p);
   clear_wh<NARROW>(s_wh);
-  const uint32_t b3 = p.b3, nd = 1u << b3, d = TidOpaque::get();
-  lds_barrier();
-  for (uint32_t i = blockIdx.x; i < G(p.big_count)[0]; i += gridDim.x) {
-    const uint32_t sb = G(p.big_list)[i];
-    const uint32_t r0 = G(p.sbstart)[sb], n = G(p.sbstart)[sb + 1] - r0;
-    const uint32_t base = (sb << b3) & f.km;
-    for (uint32_t e = d; e < (uint32_t)kMNB; e += CSize<NARROW>::THREADS) s_cur[e] = 0;
-    lds_barrier();
-    for (uint32_t j = d; j < n; j += CSize<NARROW>::THREADS) atomicAdd(&s_cur[((G(f.ik)[r0 + j] >> f.ks) - base) & f.km], 1u);
-    lds_barrier();
-    {
-      // a large sub-bucket may hold any number of records per digit: two scans
-      const uint32_t h = d < nd ? s_cur[d] : 0u;
-      uint32_t all_rec, all_present;
-      const uint32_t hst = m_block_scan<CSize<NARROW>::WAVES, TidOpaque>(h, s_tmp, &all_rec);
-      const uint32_t ex = m_block_scan<CSize<NARROW>::WAVES, TidOpaque>(h ? 1u : 0u, s_tmp, &all_present);
-      tile_groups(p, sb, 1u, r0, h, hst, ex, all_present, s_ex, s_st, s_bal);
-      lds_barrier();
-      if (d < nd) s_cur[d] = r0 + hst;
-    }
-    for (uint32_t c0 = 0; c0 < n; c0 += CSize<NARROW>::TILE) {
-      const uint32_t cnt = n - c0 < CSize<NARROW>::TILE ? n - c0 : CSize<NARROW>::TILE;
+  const uint32_t b3 = p.b3, nd = 1u << b3, d = TidOpaque::get(), n_pieces = G(p.big_count)[1];
+  for (uint32_t i = blockIdx.x; i < n_pieces; i += gridDim.x) {
+    const BigPiece q = big_piece(p, i);
+    const uint32_t base = (q.sb << b3) & f.km;
+    if (d < nd) s_cur[d] = G(p.cnt_big)[((uint64_t)i << b3) + d];
+    for (uint32_t c0 = q.lo; c0 < q.hi; c0 += CSize<NARROW>::TILE) {
+      const uint32_t cnt = q.hi - c0 < CSize<NARROW>::TILE ? q.hi - c0 : CSize<NARROW>::TILE;
       Recs<CSize<NARROW>::ITEMS> r;
-      load_c<NARROW>(f.ik, f.it, f.iw, r0 + c0, cnt, r);
+      load_c<NARROW>(f.ik, f.it, f.iw, c0, cnt, r);
+      lds_barrier();  // the wave counters are clear, the tile before is written
       uint32_t pos[CSize<NARROW>::ITEMS];
       rank_digits<RB, CSize<NARROW>::ITEMS, false, TidOpaque>(r.k, f.ks, f.km, cnt, s_wh, s_sink, pos, base);
       lds_barrier();
@@ -1075,16 +1144,16 @@ __global__ __launch_bounds__(CSize<NARROW>::THREADS) void k_msd_big_c(MsdPlan p)
       const uint32_t tot = digit_starts<CSize<NARROW>::WAVES, TidOpaque>(nd, s_wh, s_tmp, &st);
       if (d < nd) {
         const uint32_t cp = s_cur[d];
-        s_dx[d] = cp - st;  // output position minus piece position
+        s_dx[d] = cp - st;
         s_cur[d] = cp + tot;
       }
       lds_barrier();  // every digit's wave starts are in s_wh
       c_stage<NARROW>(f, r, pos, cnt, base, s_wh, s_k, s_t, s_w);
       lds_barrier();
       clear_wh<NARROW>(s_wh);
-      c_store<NARROW>(p, f, s_k, s_t, s_w, cnt, base, sb << b3, s_dx, 0u);
-      lds_barrier();
+      c_store<NARROW>(p, f, s_k, s_t, s_w, cnt, base, q.sb << b3, s_dx, 0u);
     }
+    lds_barrier();  // s_cur is rewritten by the next piece
   }
 }
 
@@ -1208,12 +1277,18 @@ hipError_t launch_msd_tiles_c(const MsdPlan& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The grids are upper bounds: with nothing listed, three empty launches.
 hipError_t launch_msd_big_c(const MsdPlan& p, hipStream_t s) {
   const bool narrow = p.b2 ? p.narrow_b : p.narrow_a;
-  const dim3 grid(p.max_big < 256u ? p.max_big : 256u);
-#define F(RB)                                                                                      \
-  if (narrow) hipLaunchKernelGGL((k_msd_big_c<RB, true>), grid, dim3(CSize<true>::THREADS), 0, s, p);          \
-  else hipLaunchKernelGGL((k_msd_big_c<RB, false>), grid, dim3(CSize<false>::THREADS), 0, s, p);
+  const dim3 pieces(std::min(p.max_pieces, 1024u));
+  if (narrow) hipLaunchKernelGGL(k_msd_big_count<true>, pieces, dim3(kCntThreads), 0, s, p);
+  else hipLaunchKernelGGL(k_msd_big_count<false>, pieces, dim3(kCntThreads), 0, s, p);
+  hipLaunchKernelGGL(k_msd_big_scan, dim3(std::min(p.max_big, 512u)), dim3(kMThreads), 0, s, p);
+#define F(RB)                                                                                             \
+  if (narrow)                                                                                              \
+    hipLaunchKernelGGL((k_msd_big_scatter<RB, true>), pieces, dim3(CSize<true>::THREADS), 0, s, p);        \
+  else                                                                                                     \
+    hipLaunchKernelGGL((k_msd_big_scatter<RB, false>), pieces, dim3(CSize<false>::THREADS), 0, s, p);
   M_RB_SWITCH(p.b3, F)
 #undef F
   return hipGetLastError();

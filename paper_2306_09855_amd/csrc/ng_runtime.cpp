@@ -1027,6 +1027,7 @@ bool msd_geometry(uint64_t N, uint32_t nn, int dbits, int log2B, uint32_t sort_r
       std::max<uint64_t>(1, std::min<uint64_t>(std::max<uint64_t>((N + 4 * piece - 1) / (4 * piece), 1024), nsb)),
       1u << 20);
   p.max_big = (uint32_t)(N / (piece + 1) + 1);
+  p.max_pieces = (uint32_t)(N / ng::kMsdBigPiece + p.max_big);
   p.n_nodes = nn;
   p.log2B = log2B;
   p.mask_words = std::max<uint32_t>(1, (1u << b3) / 32);
@@ -1084,8 +1085,10 @@ int calibrate_msd(CalSeg& g, const ng::MsdPlan& plan) {
   p.gcount = (uint32_t*)as.get(4 * (nsb + 1));
   p.gmask = (uint32_t*)as.get(4 * nsb * p.mask_words);
   p.wg_sb0 = (uint32_t*)as.get(4 * ((uint64_t)p.wgs_c + 1));
-  p.big_count = (uint32_t*)as.get(4);
-  p.big_list = (uint32_t*)as.get(4 * (uint64_t)p.max_big);
+  p.big_count = (uint32_t*)as.get(8);
+  p.big_list = (uint2*)as.get(8 * (uint64_t)p.max_big);
+  p.big_piece = (uint32_t*)as.get(4 * (uint64_t)p.max_pieces);
+  p.cnt_big = (uint32_t*)as.get((4ull * p.max_pieces) << p.b3);
   g.gp_bytes = 4 * (g.nn + 1ull);
   g.gs_bytes = 4 * g.gcap;
   release_index(c);
