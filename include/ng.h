@@ -374,9 +374,9 @@ int ng_spikes_step(ng_ctx* ctx, const uint32_t* nodes, const uint32_t* mult, uin
  * are the same with either (stable order by (source, delay), Sec. 2.2).
  *   NG_CALIB_RADIX (default): stable radix sort of all connections into a
  *     second block set, in the most-significant-digit form (below) when one
- *     context with at least 2^25 connections is calibrated, its keys
+ *     context with at least 2^23 connections is calibrated, its keys
  *     (source bits + delay bits) fit in 27 bits, its connections average at
- *     least 256 per sub-bucket and at least 10 per possible key (n_nodes x
+ *     least 256 per sub-bucket and at least 2.5 per possible key (n_nodes x
  *     2^delay bits), else in the LSD form.
  *   NG_CALIB_RADIX_MSD: the most-significant-digit form whenever one context
  *     with keys of at most 27 bits is calibrated (else LSD): a scatter by
@@ -540,13 +540,13 @@ uint64_t ng_blocks_needed(uint64_t n_conns, uint64_t n_new, uint64_t block_size,
 /* Digit plan that the default calibration (NG_CALIB_RADIX) takes for one
  * context of n_conns connections over n_nodes nodes whose delays are at most
  * max_delay steps, with sort_ranges static ranges per scatter pass (the
- * ng_set_tuning value, 1024 by default).  out[0] = 2 when the default
- * calibration takes the most-significant-digit form, 1 when only
- * NG_CALIB_RADIX_MSD takes it (fewer than 2^25 connections, too few per
- * sub-bucket or per key), 0 when
- * it does not apply (keys wider than 27 bits, n_conns = 0 or >= 2^32; the
- * rest is then zero); out[1..3] = the widths b1, b2, b3
- * of the digits from the top (b2 = 0: no second scatter); out[4], out[5] =
+ * ng_set_tuning value, 1024 by default).  out[0] = 2 when the connections
+ * are many and dense enough for the most-significant-digit form by a wide
+ * margin (at least 2^25, 256 per sub-bucket and 10 per possible key; the
+ * default calibration takes it then, and from the lower bounds given at
+ * NG_CALIB_RADIX on), 1 when the form applies otherwise, 0 when it does not
+ * apply (keys wider than 27 bits, n_conns = 0 or >= 2^32; the rest is then
+ * zero); out[1..3] = the widths b1, b2, b3 of the digits from the top (b2 = 0: no second scatter); out[4], out[5] =
  * 1 when the records after the first / second scatter pack the remaining
  * key bits and the target into one word; out[6] = workgroups of the
  * in-LDS pass; out[7] = tiles per range.  Returns NG_OK, or

@@ -153,7 +153,7 @@ hipError_t launch_set_entries(const TabEntry* d_entries, uint32_t n, hipStream_t
 // device from the counts, so no value travels back to the host.
 constexpr uint32_t kMsdTile = 10240;      // records per tile of pass A, and of B and C with unpacked records
 constexpr uint32_t kMsdTileN = 16384;     // records per tile of B with packed (8-byte) records
-constexpr uint32_t kMsdBigPiece = 65536;   // records per piece of a sub-bucket larger than one LDS load
+constexpr uint32_t kMsdBigPiece = 16384;   // records per piece of a sub-bucket larger than one LDS load
 constexpr uint32_t kMsdMaxDigit = 9;      // widest digit
 constexpr uint32_t kMsdMaxKeyBits = 27;   // 3 x kMsdMaxDigit
 
@@ -169,6 +169,8 @@ struct MsdPlan {
   uint32_t ranges_b;                // ranges of pass B wanted (spread over the buckets by their tiles)
   uint32_t max_ranges_b;            // ranges of pass B: at most this many
   uint32_t wgs_c;                   // workgroups of pass C
+  uint32_t nsb_used;                // sub-buckets that keys below n_nodes << dbits reach
+  uint32_t sb_cost;                 // work of a sub-bucket in pass C beside its records, in records
   uint32_t n_nodes;
   int log2B;
   char* const* in_blocks;           // creation-order blocks
@@ -197,6 +199,19 @@ struct MsdPlan {
   uint32_t* group_start;            // [min(n, 2^keybits) + 1]
   uint32_t* n_groups;               // G (device word)
 };
+
+constexpr uint32_t kCMaxSub = 63;      // sub-buckets per tile of pass C: lanes 1..63 test the ends
+
+// Sub-buckets per tile: bounded by the lanes of one wave, by 9-bit combined
+// digits, and for packed records by the sub-bucket bits they hold.
+__host__ __device__ inline uint32_t msd_max_sub(const MsdPlan& p, bool narrow) {
+  uint32_t m = kCMaxSub < (512u >> p.b3) ? kCMaxSub : (512u >> p.b3);
+  if (narrow) {
+    const uint32_t own = 1u << (p.cbits - p.b3);
+    m = m < own ? m : own;
+  }
+  return m;
+}
 
 // Records pass C sorts in LDS at once: runs of whole sub-buckets up to this
 // many records form one tile; a larger sub-bucket is sorted in pieces of

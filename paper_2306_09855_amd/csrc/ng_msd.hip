@@ -106,8 +106,10 @@ __device__ __forceinline__ uint32_t m_range(uint32_t per_xcd) {
 
 // ---------------------------------------------------------------------------
 // Tile records in registers.  Item k of wave w is tile record
-// w * ITEMS * 64 + k * 64 + lane (64 consecutive records per item slot), so
-// ranks computed slot by slot follow the record order.
+// w * span + k * 64 + lane (64 consecutive records per item slot), so ranks
+// computed slot by slot follow the record order.  span = ITEMS * 64; pass C
+// spreads a tile that is not full over all waves with a smaller one (slots at
+// or past it hold no record).
 // ---------------------------------------------------------------------------
 template <int ITEMS>
 struct Recs {
@@ -117,9 +119,9 @@ struct Recs {
 };
 
 template <class TID = TidPlain>
-__device__ __forceinline__ uint32_t item_index(int ITEMS, int k) {
-  const int lane = TID::get() & 63, wave = TID::get() >> 6;
-  return (uint32_t)(wave * ITEMS * 64 + k * 64 + lane);
+__device__ __forceinline__ uint32_t item_index(uint32_t span, int k) {
+  const uint32_t lane = TID::get() & 63, wave = TID::get() >> 6;
+  return wave * span + (uint32_t)(k * 64) + lane;
 }
 
 // Records [base, base + cnt) of the creation-order blocks (a tile spans at
@@ -135,7 +137,7 @@ __device__ __forceinline__ void load_blocks(char* const* blocks, int log2B, uint
 // record arrays stay in registers.
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
-    const uint32_t lj = item_index(ITEMS, k);
+    const uint32_t lj = item_index(ITEMS * 64, k);
     uint32_t kv = 0, tv = 0, wv = 0;
     if (FULL || lj < cnt) {
       const uint32_t j = base + lj;
@@ -154,12 +156,12 @@ __device__ __forceinline__ void load_blocks(char* const* blocks, int log2B, uint
 
 template <int ITEMS, int IN, bool FULL, class TID = TidPlain>
 __device__ __forceinline__ void load_arrays(const uint32_t* ik, const uint32_t* it, const uint32_t* iw,
-                                            uint32_t base, uint32_t cnt, Recs<ITEMS>& r) {
+                                            uint32_t base, uint32_t cnt, Recs<ITEMS>& r, uint32_t span = ITEMS * 64) {
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
-    const uint32_t lj = item_index<TID>(ITEMS, k);
+    const uint32_t lj = item_index<TID>(span, k);
     uint32_t kv = 0, tv = 0, wv = 0;
-    if (FULL || lj < cnt) {
+    if (FULL || ((uint32_t)(k * 64) < span && lj < cnt)) {
       kv = G(ik)[base + lj];
       if constexpr (IN == IN_WIDE) tv = G(it)[base + lj];
       wv = G(iw)[base + lj];
@@ -184,16 +186,16 @@ __device__ __forceinline__ void load_arrays(const uint32_t* ik, const uint32_t* 
 template <int RB, int ITEMS, bool FULL, class TID = TidPlain>
 __device__ __forceinline__ void rank_digits(const uint32_t (&key)[ITEMS], uint32_t shift, uint32_t mask, uint32_t cnt,
                                             uint32_t* wh, uint32_t* sink, uint32_t (&pos)[ITEMS],
-                                            uint32_t base = 0, uint32_t nbits = RB) {
+                                            uint32_t base = 0, uint32_t nbits = RB, uint32_t span = ITEMS * 64) {
   constexpr int kLag = 4;
   const int lane = TID::get() & 63, wave = TID::get() >> 6;
   uint32_t prv[ITEMS];
   // slots past the tile's end hold no record of this wave (a uniform test)
-  auto slot_used = [&](int k) { return FULL || (uint32_t)(wave * ITEMS * 64 + k * 64) < cnt; };
+  auto slot_used = [&](int k) { return FULL || ((uint32_t)(k * 64) < span && wave * span + (uint32_t)(k * 64) < cnt); };
 #pragma unroll
   for (int k = 0; k < ITEMS + kLag; ++k) {
     if (k < ITEMS && slot_used(k)) {
-      const uint32_t lj = (uint32_t)(wave * ITEMS * 64 + k * 64 + lane);
+      const uint32_t lj = wave * span + (uint32_t)(k * 64 + lane);
       const bool valid = FULL || lj < cnt;
       const uint32_t d = ((key[k] >> shift) - base) & mask;
       uint32_t plo = ~0u, phi = ~0u;
@@ -358,7 +360,7 @@ __device__ __forceinline__ void scatter_tile(const PassIO& io, uint32_t cnt, con
   lds_barrier();
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
-    if (FULL || item_index(ITEMS, k) < cnt) {
+    if (FULL || item_index(ITEMS * 64, k) < cnt) {
       const uint32_t p = pos[k] + wh_get(L.wh, wave, (r.k[k] >> io.shift) & io.mask);
       L.k[p] = r.k[k];
       if constexpr (HAS_T) L.t[p] = r.t[k];
@@ -717,21 +719,25 @@ __global__ __launch_bounds__(256) void k_msd_zero(MsdPlan p) {
   for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < nsb * p.mask_words; i += stride) G(p.gmask)[i] = 0;
 }
 
-// Workgroup w of pass C takes the sub-buckets whose first record lies in
-// [w * n / wgs, (w + 1) * n / wgs): a split by records.
+// The sub-buckets [wg_sb0[w], wg_sb0[w + 1]) of workgroup w of pass C: an even
+// split of their work, a record counting 1 and a sub-bucket sb_cost (its
+// share of a tile's fixed cost), so that a workgroup in a sparse stretch does
+// not walk many more tiles than the others (the work before sub-bucket i is
+// sbstart[i] + i * sb_cost).  Split by records alone, pass C took 6.7 ms
+// instead of 1.4 for 5.3e7 connections over 1e6 nodes (0.8 per possible
+// key), and 3.4 instead of 2.2 for the 4,096-call batch.
 __global__ __launch_bounds__(256) void k_msd_split(MsdPlan p) {
-  const uint32_t nsb = 1u << (p.b1 + p.b2);
   const uint32_t w = blockIdx.x * 256u + threadIdx.x;
   if (w < 2) p.big_count[w] = 0;  // sub-buckets and pieces listed by pass C
   if (w > p.wgs_c) return;
   // the last boundary is the first sub-bucket past the records: the empty
   // sub-buckets above it are never visited (their group counts and masks are
   // zero from k_msd_zero)
-  const uint32_t target = (uint32_t)((uint64_t)w * p.n / p.wgs_c);
-  uint32_t lo = 0, hi = nsb;  // first sb with sbstart[sb] >= target
+  const uint64_t target = (uint64_t)w * (p.n + (uint64_t)p.nsb_used * p.sb_cost) / p.wgs_c;
+  uint32_t lo = 0, hi = p.nsb_used;  // first sb with at least the target's work before it
   while (lo < hi) {
     const uint32_t mid = (lo + hi) >> 1;
-    if (p.sbstart[mid] < target) lo = mid + 1;
+    if (p.sbstart[mid] + (uint64_t)mid * p.sb_cost < target) lo = mid + 1;
     else hi = mid;
   }
   p.wg_sb0[w] = lo;
@@ -765,19 +771,6 @@ struct CSize {
   static constexpr int WH_WORDS = WAVES / 2 * kMNB;
   static_assert(WAVES % 2 == 0 && THREADS >= kMNB, "pass C waves");
 };
-constexpr uint32_t kCMaxSub = 63;      // sub-buckets per tile: lanes 1..63 test the ends
-
-// Sub-buckets per tile: bounded by the lanes of one wave, by 9-bit combined
-// digits, and for packed records by the sub-bucket bits they hold.
-__host__ __device__ inline uint32_t msd_max_sub(const MsdPlan& p, bool narrow) {
-  uint32_t m = kCMaxSub < (512u >> p.b3) ? kCMaxSub : (512u >> p.b3);
-  if (narrow) {
-    const uint32_t own = 1u << (p.cbits - p.b3);
-    m = m < own ? m : own;
-  }
-  return m;
-}
-
 struct CTile {
   uint32_t sb, e, r0, r1;  // sub-buckets [sb, e), records [r0, r1); e == sb: no tile left
 };
@@ -813,12 +806,22 @@ __device__ __forceinline__ CTile tile_finish(uint32_t st, uint32_t sb, uint32_t 
   return t;
 }
 
+// Records of each wave's span of a tile of cnt records: the tile's 64-record
+// slots spread evenly over the waves, so that all of them rank and stage a
+// tile that is not full (3e8 microcircuit, tiles 95% full: 1.62 -> 1.55 ms;
+// the 4,096-call batch, tiles a quarter full: 4.1 -> 3.4 ms).
+template <bool NARROW>
+__device__ __forceinline__ uint32_t c_span(uint32_t cnt) {
+  return (cnt + CSize<NARROW>::THREADS - 1) / CSize<NARROW>::THREADS * 64u;
+}
+
 // One predicated form of each step: pass C keeps a single copy of its
 // load and ranking, which keeps its loop within the register file.
 template <bool NARROW>
 __device__ __forceinline__ void load_c(const uint32_t* ik, const uint32_t* it, const uint32_t* iw, uint32_t base,
                                        uint32_t cnt, Recs<CSize<NARROW>::ITEMS>& r) {
-  load_arrays<CSize<NARROW>::ITEMS, NARROW ? IN_NARROW : IN_WIDE, false, TidOpaque>(ik, it, iw, base, cnt, r);
+  load_arrays<CSize<NARROW>::ITEMS, NARROW ? IN_NARROW : IN_WIDE, false, TidOpaque>(ik, it, iw, base, cnt, r,
+                                                                                  c_span<NARROW>(cnt));
 }
 
 template <bool NARROW>
@@ -938,9 +941,10 @@ __device__ __forceinline__ void c_stage(const CFields& f, const Recs<CSize<NARRO
                                         uint32_t cnt, uint32_t base, const uint32_t* s_wh, uint32_t* s_k, uint32_t* s_t,
                                         uint32_t* s_w) {
   const int wave = TidOpaque::get() >> 6;
+  const uint32_t span = c_span<NARROW>(cnt);
 #pragma unroll
   for (int k = 0; k < CSize<NARROW>::ITEMS; ++k) {
-    if (item_index<TidOpaque>(CSize<NARROW>::ITEMS, k) < cnt) {
+    if ((uint32_t)(k * 64) < span && item_index<TidOpaque>(span, k) < cnt) {
       const uint32_t dg = ((r.k[k] >> f.ks) - base) & f.km;
       const uint32_t q = pos[k] + wh_get(s_wh, wave, dg);
       s_k[q] = r.k[k];
@@ -1010,7 +1014,7 @@ __global__ __launch_bounds__(CSize<NARROW>::THREADS, CSize<NARROW>::WAVES_PER_SI
       uint32_t nbits = 1;
       while ((1u << nbits) < nd) ++nbits;
       uint32_t pos[ITEMS];
-      rank_digits<RB, ITEMS, false, TidOpaque>(r.k, f.ks, f.km, n, s_wh, s_sink, pos, base, nbits);
+      rank_digits<RB, ITEMS, false, TidOpaque>(r.k, f.ks, f.km, n, s_wh, s_sink, pos, base, nbits, c_span<NARROW>(n));
       if (wave == 0) {
         const CTile t = tile_finish(probe, cur.e, lim, f.msub, TILE);
         if (lane == 0) s_next[par] = t;
@@ -1045,8 +1049,9 @@ __global__ __launch_bounds__(CSize<NARROW>::THREADS, CSize<NARROW>::WAVES_PER_SI
 // sub-bucket's counts into every piece's first output position per D3 value
 // and records its groups, and k_msd_big_scatter sorts each piece, one load
 // after another, to those positions.  (One workgroup per sub-bucket took 5.3
-// ms of the 4,096-call batch, whose calls draw from as little as one source;
-// in pieces: see launch_msd_big_c.)
+// ms of the 4,096-call batch, whose calls draw from as little as one source
+// -- 1.7e8 of its 4.4e8 records are in such sub-buckets; in pieces 2.0 ms.
+// Pieces of 65,536 records: 0.22 ms instead of 0.14 at 3.3e7 connections.)
 struct BigPiece {
   uint32_t sb, lo, hi;  // records [lo, hi) of sub-bucket sb
 };
@@ -1132,13 +1137,15 @@ __global__ __launch_bounds__(CSize<NARROW>::THREADS, CSize<NARROW>::WAVES_PER_SI
     const BigPiece q = big_piece(p, i);
     const uint32_t base = (q.sb << b3) & f.km;
     if (d < nd) s_cur[d] = G(p.cnt_big)[((uint64_t)i << b3) + d];
+    auto tile_cnt = [&](uint32_t c0) { return q.hi - c0 < CSize<NARROW>::TILE ? q.hi - c0 : CSize<NARROW>::TILE; };
+    Recs<CSize<NARROW>::ITEMS> r;
+    load_c<NARROW>(f.ik, f.it, f.iw, q.lo, tile_cnt(q.lo), r);
     for (uint32_t c0 = q.lo; c0 < q.hi; c0 += CSize<NARROW>::TILE) {
-      const uint32_t cnt = q.hi - c0 < CSize<NARROW>::TILE ? q.hi - c0 : CSize<NARROW>::TILE;
-      Recs<CSize<NARROW>::ITEMS> r;
-      load_c<NARROW>(f.ik, f.it, f.iw, c0, cnt, r);
+      const uint32_t cnt = tile_cnt(c0);
       lds_barrier();  // the wave counters are clear, the tile before is written
       uint32_t pos[CSize<NARROW>::ITEMS];
-      rank_digits<RB, CSize<NARROW>::ITEMS, false, TidOpaque>(r.k, f.ks, f.km, cnt, s_wh, s_sink, pos, base);
+      rank_digits<RB, CSize<NARROW>::ITEMS, false, TidOpaque>(r.k, f.ks, f.km, cnt, s_wh, s_sink, pos, base, b3,
+                                                              c_span<NARROW>(cnt));
       lds_barrier();
       uint32_t st;
       const uint32_t tot = digit_starts<CSize<NARROW>::WAVES, TidOpaque>(nd, s_wh, s_tmp, &st);
@@ -1151,6 +1158,8 @@ __global__ __launch_bounds__(CSize<NARROW>::THREADS, CSize<NARROW>::WAVES_PER_SI
       c_stage<NARROW>(f, r, pos, cnt, base, s_wh, s_k, s_t, s_w);
       lds_barrier();
       clear_wh<NARROW>(s_wh);
+      // the next tile's records load while this one is written
+      if (c0 + cnt < q.hi) load_c<NARROW>(f.ik, f.it, f.iw, c0 + cnt, tile_cnt(c0 + cnt), r);
       c_store<NARROW>(p, f, s_k, s_t, s_w, cnt, base, q.sb << b3, s_dx, 0u);
     }
     lds_barrier();  // s_cur is rewritten by the next piece

@@ -1016,16 +1016,22 @@ bool msd_geometry(uint64_t N, uint32_t nn, int dbits, int log2B, uint32_t sort_r
   // network's: 0.78 ms at three times against 0.83 at twice)
   p.ranges_b = 3 * std::max<uint32_t>(sort_ranges, 1);
   p.max_ranges_b = b2 ? (uint32_t)(p.ranges_b + (1ull << b1)) : 0u;
-  // pass C: workgroups of about four LDS loads of records each (3e8
+  // pass C: workgroups of about four LDS loads of work each (3e8
   // microcircuit: 1.62 ms; three loads 1.64, six 1.64, ten 1.65, twenty
-  // 1.79), and at least 1,024 (two rounds of two workgroups per CU) so that
-  // short tiles of few records -- small or sparse calibrations -- still
-  // spread over the chip; no more workgroups than sub-buckets
-  const uint64_t piece = ng::msd_cap(b2 ? p.narrow_b : p.narrow_a);
+  // 1.79), in whole rounds of 512 (two workgroups per CU) and at least two
+  // rounds, so that short tiles of few records still spread over the chip; no
+  // more workgroups than sub-buckets.  A tile's fixed cost (barriers, scans, the latency of
+  // its loads) is that of about kTileCost records, shared by the sub-buckets
+  // a tile holds at most.
+  constexpr uint32_t kTileCost = 3072;
+  const bool nar = b2 ? p.narrow_b : p.narrow_a;
+  const uint64_t piece = ng::msd_cap(nar);
   const uint64_t nsb = 1ull << (b1 + b2);
-  p.wgs_c = (uint32_t)std::min<uint64_t>(
-      std::max<uint64_t>(1, std::min<uint64_t>(std::max<uint64_t>((N + 4 * piece - 1) / (4 * piece), 1024), nsb)),
-      1u << 20);
+  p.nsb_used = (uint32_t)std::min<uint64_t>(nsb, (keyspace + (1ull << b3) - 1) >> b3);
+  p.sb_cost = std::max<uint32_t>(1, kTileCost / ng::msd_max_sub(p, nar));
+  const uint64_t work = N + (uint64_t)p.nsb_used * p.sb_cost;
+  const uint64_t rounds = std::max<uint64_t>((work / (4 * piece) + 256) / 512, 2);
+  p.wgs_c = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, std::min<uint64_t>(512 * rounds, nsb)), 1u << 20);
   p.max_big = (uint32_t)(N / (piece + 1) + 1);
   p.max_pieces = (uint32_t)(N / ng::kMsdBigPiece + p.max_big);
   p.n_nodes = nn;
@@ -1035,17 +1041,25 @@ bool msd_geometry(uint64_t N, uint32_t nn, int dbits, int log2B, uint32_t sort_r
 }
 
 // The default radix calibration takes the most-significant-digit form when
-// (1) there are at least 2^25 connections: below, the LSD passes are faster
-// (measured on MI355X: 0.94 against 1.04 ms at 3e7 connections over 77,169
-// nodes, 2.9 against 2.3 ms at 1e8); (2) the sub-buckets it must visit hold
-// 256 connections on average or more (fewer connections over a wide key
-// leave most sub-buckets empty); and (3) the 512 keys that one LDS tile can
-// tell apart hold at least half a tile of connections (n >= 10 connections
-// per possible key: otherwise pass C sorts nearly empty tiles).
+// (1) there are at least 2^23 connections: below, the LSD passes need fewer
+// launches (calibration at 24 connections per possible key, LSD against MSD:
+// 0.20 and 0.20 ms at 4e6, 0.31 and 0.30 at 8e6, 0.42 and 0.36 at 1.2e7, 1.60
+// and 1.22 at 6e7); (2) the sub-buckets it must visit hold 256 connections on
+// average or more; and (3) there are at least 2.5 connections per possible
+// key (below, pass C sorts nearly empty tiles of 512 keys: 1.74 and 1.73 ms
+// at 2.8 per key and 5.4e7 uneven connections, 0.95 and 1.13 at 2.3 and
+// 2.9e7, 2.0 and 2.6 at 0.8 and 5.3e7; 14.4 and 11.0 at 6.9 and 4.4e8).
 bool msd_pays(const ng::MsdPlan& p) {
   const uint64_t keyspace = (uint64_t)p.n_nodes << p.dbits;
-  return p.n >= (1u << 25) && (uint64_t)p.n >= (256ull << (p.b1 + p.b2)) &&
-         (uint64_t)p.n * 512 >= keyspace * (ng::kMsdTile / 2);
+  return p.n >= (1u << 23) && (uint64_t)p.n >= (256ull << (p.b1 + p.b2)) && (uint64_t)p.n * 2 >= keyspace * 5;
+}
+
+// The plan query's "2": large and dense enough that the form pays by a wide
+// margin (at least 2^25 connections and 10 per possible key); msd_pays holds
+// for every such plan.
+bool msd_dense(const ng::MsdPlan& p) {
+  const uint64_t keyspace = (uint64_t)p.n_nodes << p.dbits;
+  return msd_pays(p) && p.n >= (1u << 25) && (uint64_t)p.n * 512 >= keyspace * (ng::kMsdTile / 2);
 }
 
 // Calibration of one context by the most-significant-digit sort: count and
@@ -1504,7 +1518,7 @@ int ng_calibration_plan(uint64_t n_conns, uint32_t n_nodes, int32_t max_delay, u
   ng::MsdPlan p;
   if (!msd_geometry(n_conns, n_nodes, bitwidth((uint64_t)max_delay), 24, sort_ranges ? sort_ranges : 1024, p))
     return NG_OK;
-  const uint32_t v[8] = {msd_pays(p) ? 2u : 1u, p.b1, p.b2, p.b3, p.narrow_a, p.narrow_b, p.wgs_c, p.tpr};
+  const uint32_t v[8] = {msd_dense(p) ? 2u : 1u, p.b1, p.b2, p.b3, p.narrow_a, p.narrow_b, p.wgs_c, p.tpr};
   for (int i = 0; i < 8; ++i) out[i] = v[i];
   return NG_OK;
 }
