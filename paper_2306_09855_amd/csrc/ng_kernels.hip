@@ -108,14 +108,17 @@ __global__ __launch_bounds__(kGenThreads) void k_generate_batch(const GenDesc* _
 //              buffer), runs of equal digits stored to consecutive positions;
 //              stores that fill whole 128-byte lines are marked streaming.
 // Tiles are large (10,240 records, 512 threads) because the cost of a pass
-// is set by the length of the runs each tile writes per digit.  Ranges are
+// is set by the length of the runs each tile writes per digit.  A pass over
+// few records takes tiles of 2,048 instead, as large tiles leave most of the
+// chip idle and a tile's serial phases set the time (sort_small_tiles;
+// downsweeps of a calibration, tiles of 10,240 and 2,048: 40 and 16 us at
+// 3e5 records, 104 and 73 at 4e6, 200 and 181 at 8e6).  Ranges are
 // XCD-aware: workgroup w runs on XCD w % 8, and each XCD owns a contiguous
 // span of ranges, so the runs written by neighbouring ranges meet in one L2.
 // ---------------------------------------------------------------------------
 constexpr int kSortThreads = 512;
 constexpr int kSortWaves = kSortThreads / 64;
-constexpr int kItems = 20;
-constexpr int kTile = kSortThreads * kItems;  // 10,240 records
+constexpr int kItemsLarge = 20, kItemsSmall = 4;  // records per thread: tiles of 10,240 and 2,048
 constexpr int kMaxRadixBits = 9;
 
 
@@ -133,7 +136,9 @@ __device__ __forceinline__ int range_index(const SortPack& pk) {
 struct RangeTiles {
   uint32_t start, n_full, tail;
 };
+template <int ITEMS>
 __device__ __forceinline__ RangeTiles range_tiles(const SortSeg& sg, uint32_t r) {
+  constexpr int kTile = kSortThreads * ITEMS;
   RangeTiles t;
   const uint32_t tpr = sg.tiles_per_range;
   t.start = r * tpr * (uint32_t)kTile;  // r < n_ranges, so start < n
@@ -181,9 +186,9 @@ __device__ __forceinline__ uint32_t load_blocked_key(const SortIO& io, const Til
 constexpr int kHistCopies = 4;
 static_assert(kHistCopies == 4, "word 4d + c, read back as one uint4 (16-byte aligned array)");
 
-template <int RB, bool IN_BLOCKED>
+template <int RB, bool IN_BLOCKED, int ITEMS>
 __global__ __launch_bounds__(kSortThreads) void k_upsweep(SortPack pk, uint32_t* __restrict__ counts) {
-  constexpr int NB = 1 << RB;
+  constexpr int NB = 1 << RB, kTile = kSortThreads * ITEMS;
   __shared__ __align__(16) uint32_t hist[NB * kHistCopies];
   const int gr = range_index(pk);
   if (gr < 0) return;
@@ -194,21 +199,21 @@ __global__ __launch_bounds__(kSortThreads) void k_upsweep(SortPack pk, uint32_t*
   const uint32_t copy = threadIdx.x & (kHistCopies - 1);
   for (uint32_t d = threadIdx.x; d < nd * kHistCopies; d += kSortThreads) hist[d] = 0;
   __syncthreads();
-  const RangeTiles rt = range_tiles(sg, r);
+  const RangeTiles rt = range_tiles<ITEMS>(sg, r);
   for (uint32_t t = 0; t < rt.n_full; ++t) {
     const uint64_t base = rt.start + t * (uint32_t)kTile;
     const uint32_t cnt = kTile;
-    uint32_t key[kItems];
+    uint32_t key[ITEMS];
     // A full tile with 16-byte loads: 4 consecutive records per load (the
     // order of records does not matter to a histogram).  base is a
     // multiple of 4 records and so is every block size, so a group of 4
     // never straddles two blocks and every load is aligned.
-    static_assert(kItems % 4 == 0, "vector loads of 4 records");
+    static_assert(ITEMS % 4 == 0, "vector loads of 4 records");
     if constexpr (IN_BLOCKED) {
       const TileSrc ts = tile_src(io, base, cnt);
       const uint64_t B = 1ull << io.log2B;
 #pragma unroll
-      for (int v = 0; v < kItems / 4; ++v) {
+      for (int v = 0; v < ITEMS / 4; ++v) {
         const uint64_t j = base + 4ull * (v * kSortThreads + threadIdx.x);
         const char* blk = ts.blk[(j >> io.log2B) != ts.first_block];
         const uint64_t o = j & (B - 1);
@@ -221,7 +226,7 @@ __global__ __launch_bounds__(kSortThreads) void k_upsweep(SortPack pk, uint32_t*
       }
     } else {
 #pragma unroll
-      for (int v = 0; v < kItems / 4; ++v) {
+      for (int v = 0; v < ITEMS / 4; ++v) {
         const u32x4 k4 = *(const NG_GLOBAL u32x4*)(io.in_keys + base + 4ull * (v * kSortThreads + threadIdx.x));
         key[4 * v + 0] = k4.x;
         key[4 * v + 1] = k4.y;
@@ -230,34 +235,35 @@ __global__ __launch_bounds__(kSortThreads) void k_upsweep(SortPack pk, uint32_t*
       }
     }
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) atomicAdd(&hist[(((key[k] >> shift) & mask) << 2) | copy], 1u);
+    for (int k = 0; k < ITEMS; ++k) atomicAdd(&hist[(((key[k] >> shift) & mask) << 2) | copy], 1u);
   }
   if (rt.tail) {  // the ragged last tile of the segment
     const uint64_t base = rt.start + rt.n_full * (uint32_t)kTile;
     const uint32_t cnt = rt.tail;
-    uint32_t key[kItems];
+    uint32_t key[ITEMS];
     if constexpr (IN_BLOCKED) {
       const TileSrc ts = tile_src(io, base, cnt);
 #pragma unroll
-      for (int k = 0; k < kItems; ++k) {
+      for (int k = 0; k < ITEMS; ++k) {
         const uint32_t lj = k * kSortThreads + threadIdx.x;
         key[k] = lj < cnt ? load_blocked_key(io, ts, base + lj) : 0u;
       }
     } else {
 #pragma unroll
-      for (int k = 0; k < kItems; ++k) {
+      for (int k = 0; k < ITEMS; ++k) {
         const uint32_t lj = k * kSortThreads + threadIdx.x;
         key[k] = lj < cnt ? G(io.in_keys)[base + lj] : 0u;
       }
     }
 #pragma unroll
-    for (int k = 0; k < kItems; ++k)
+    for (int k = 0; k < ITEMS; ++k)
       if ((uint32_t)(k * kSortThreads + threadIdx.x) < cnt) atomicAdd(&hist[(((key[k] >> shift) & mask) << 2) | copy], 1u);
   }
   __syncthreads();
   for (uint32_t d = threadIdx.x; d < nd; d += kSortThreads) {
     const uint4 h = *reinterpret_cast<const uint4*>(&hist[d << 2]);
-    counts[sg.cbase + (uint64_t)d * sg.n_ranges + r] = h.x + h.y + h.z + h.w;
+    const uint64_t at = pk.self_offsets ? ((uint64_t)r << sg.nbits) + d : (uint64_t)d * sg.n_ranges + r;
+    counts[sg.cbase + at] = h.x + h.y + h.z + h.w;
   }
 }
 
@@ -286,35 +292,35 @@ __device__ __forceinline__ char* out_block(const SortIO& io, const SortLds& L, u
 }
 
 // Records of one tile into registers: wave w owns tile records
-// [w*kItems*64, (w+1)*kItems*64), 64 consecutive records per item slot.
-template <bool IN_BLOCKED, bool FULL>
-__device__ __forceinline__ void load_keys(const SortIO& io, uint64_t base, uint32_t cnt, uint32_t (&key)[kItems]) {
+// [w*ITEMS*64, (w+1)*ITEMS*64), 64 consecutive records per item slot.
+template <bool IN_BLOCKED, bool FULL, int ITEMS>
+__device__ __forceinline__ void load_keys(const SortIO& io, uint64_t base, uint32_t cnt, uint32_t (&key)[ITEMS]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if constexpr (IN_BLOCKED) {
     const TileSrc ts = tile_src(io, base, cnt);
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-      const uint32_t lj = (uint32_t)(wave * kItems * 64 + k * 64 + lane);
+    for (int k = 0; k < ITEMS; ++k) {
+      const uint32_t lj = (uint32_t)(wave * ITEMS * 64 + k * 64 + lane);
       key[k] = (FULL || lj < cnt) ? load_blocked_key(io, ts, base + lj) : 0u;
     }
   } else {
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-      const uint32_t lj = (uint32_t)(wave * kItems * 64 + k * 64 + lane);
+    for (int k = 0; k < ITEMS; ++k) {
+      const uint32_t lj = (uint32_t)(wave * ITEMS * 64 + k * 64 + lane);
       key[k] = (FULL || lj < cnt) ? G(io.in_keys)[base + lj] : 0u;
     }
   }
 }
 
-template <bool IN_BLOCKED, bool FULL>
-__device__ __forceinline__ void load_pays(const SortIO& io, uint64_t base, uint32_t cnt, uint2 (&pay)[kItems]) {
+template <bool IN_BLOCKED, bool FULL, int ITEMS>
+__device__ __forceinline__ void load_pays(const SortIO& io, uint64_t base, uint32_t cnt, uint2 (&pay)[ITEMS]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t B = 1ull << io.log2B;
   if constexpr (IN_BLOCKED) {
     const TileSrc ts = tile_src(io, base, cnt);
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-      const uint32_t lj = (uint32_t)(wave * kItems * 64 + k * 64 + lane);
+    for (int k = 0; k < ITEMS; ++k) {
+      const uint32_t lj = (uint32_t)(wave * ITEMS * 64 + k * 64 + lane);
       if (FULL || lj < cnt) {
         const uint64_t j = base + lj;
         const char* blk = ts.blk[(j >> io.log2B) != ts.first_block];
@@ -327,17 +333,17 @@ __device__ __forceinline__ void load_pays(const SortIO& io, uint64_t base, uint3
     }
   } else {
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-      const uint32_t lj = (uint32_t)(wave * kItems * 64 + k * 64 + lane);
+    for (int k = 0; k < ITEMS; ++k) {
+      const uint32_t lj = (uint32_t)(wave * ITEMS * 64 + k * 64 + lane);
       pay[k] = (FULL || lj < cnt) ? ld_u32x2(io.in_pay + base + lj) : make_uint2(0, 0);
     }
   }
 }
 
-template <bool IN_BLOCKED>
-__device__ __forceinline__ void load_keys_any(const SortIO& io, uint64_t base, uint32_t cnt, uint32_t (&key)[kItems]) {
-  if (cnt == kTile) load_keys<IN_BLOCKED, true>(io, base, cnt, key);
-  else load_keys<IN_BLOCKED, false>(io, base, cnt, key);
+template <bool IN_BLOCKED, int ITEMS>
+__device__ __forceinline__ void load_keys_any(const SortIO& io, uint64_t base, uint32_t cnt, uint32_t (&key)[ITEMS]) {
+  if (cnt == (uint32_t)(kSortThreads * ITEMS)) load_keys<IN_BLOCKED, true, ITEMS>(io, base, cnt, key);
+  else load_keys<IN_BLOCKED, false, ITEMS>(io, base, cnt, key);
 }
 
 // Store of one payload to its sorted position: streaming where the run fills
@@ -376,22 +382,22 @@ __device__ __forceinline__ void store_pay(const SortIO& io, const SortLds& L, ui
 // atomic (the other lanes add to a private word), and the value it gets back
 // reaches its peers through a lane permute a few slots later, so no slot
 // waits on the one before it.
-template <int RB, bool IN_BLOCKED, bool OUT_BLOCKED, bool FULL>
+template <int RB, bool IN_BLOCKED, bool OUT_BLOCKED, bool FULL, int ITEMS>
 __device__ __forceinline__ void sort_tile(const SortIO& io, uint64_t base, uint32_t cnt, uint32_t shift,
-                                          uint32_t nbits, const SortLds& L, uint32_t (&key)[kItems],
-                                          uint2 (&pay)[kItems], uint64_t next_base, uint32_t next_cnt) {
+                                          uint32_t nbits, const SortLds& L, uint32_t (&key)[ITEMS],
+                                          uint2 (&pay)[ITEMS], uint64_t next_base, uint32_t next_cnt) {
   constexpr int NB = 1 << RB;
   constexpr int kLag = 4;  // slots between a counter add and the permute of its result
   const uint32_t nd = 1u << nbits, mask = nd - 1;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t B = 1ull << io.log2B;
 
-  uint32_t pos[kItems];  // rank: (peers below) | (lowest peer's lane << 8), then the rank itself
-  uint32_t prv[kItems];  // counter value returned to the lowest peer
+  uint32_t pos[ITEMS];  // rank: (peers below) | (lowest peer's lane << 8), then the rank itself
+  uint32_t prv[ITEMS];  // counter value returned to the lowest peer
 #pragma unroll
-  for (int k = 0; k < kItems + kLag; ++k) {
-    if (k < kItems) {
-      const uint32_t lj = (uint32_t)(wave * kItems * 64 + k * 64 + lane);
+  for (int k = 0; k < ITEMS + kLag; ++k) {
+    if (k < ITEMS) {
+      const uint32_t lj = (uint32_t)(wave * ITEMS * 64 + k * 64 + lane);
       const bool valid = FULL || lj < cnt;
       const uint32_t dg = (key[k] >> shift) & mask;
       uint32_t plo = ~0u, phi = ~0u;
@@ -454,8 +460,8 @@ __device__ __forceinline__ void sort_tile(const SortIO& io, uint64_t base, uint3
 
   // phase 1: keys staged by digit, stored as runs of equal digits
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const uint32_t lj = (uint32_t)(wave * kItems * 64 + k * 64 + lane);
+  for (int k = 0; k < ITEMS; ++k) {
+    const uint32_t lj = (uint32_t)(wave * ITEMS * 64 + k * 64 + lane);
     if (FULL || lj < cnt) {
       const uint32_t dg = (key[k] >> shift) & mask;
       pos[k] += L.wh[wave * NB + dg];
@@ -467,10 +473,10 @@ __device__ __forceinline__ void sort_tile(const SortIO& io, uint64_t base, uint3
   // partial lines at a run's ends stay cached, so that the neighbouring
   // tile's run can complete them in L2 before they reach HBM.
   const uint32_t dmask = (1u << io.dbits) - 1;
-  uint32_t dest[kItems];
+  uint32_t dest[ITEMS];
   uint32_t inner = 0;  // bit k: record k lies in a completely filled line
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
+  for (int k = 0; k < ITEMS; ++k) {
     const uint32_t lp = (uint32_t)(k * kSortThreads + threadIdx.x);
     if (FULL || lp < cnt) {
       const uint32_t kk = L.key[lp];
@@ -494,8 +500,8 @@ __device__ __forceinline__ void sort_tile(const SortIO& io, uint64_t base, uint3
   // phase 2: payloads through their own buffer (the counters are free again
   // once every wave has read its positions above)
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const uint32_t lj = (uint32_t)(wave * kItems * 64 + k * 64 + lane);
+  for (int k = 0; k < ITEMS; ++k) {
+    const uint32_t lj = (uint32_t)(wave * ITEMS * 64 + k * 64 + lane);
     if (FULL || lj < cnt) L.pay[pos[k]] = pay[k];
   }
   for (uint32_t d = threadIdx.x; d < nd; d += kSortThreads) {
@@ -503,18 +509,19 @@ __device__ __forceinline__ void sort_tile(const SortIO& io, uint64_t base, uint3
     for (int v = 0; v < kSortWaves; ++v) L.wh[v * NB + d] = 0;
   }
   lds_barrier();
-  if (next_cnt) load_keys_any<IN_BLOCKED>(io, next_base, next_cnt, key);
+  if (next_cnt) load_keys_any<IN_BLOCKED, ITEMS>(io, next_base, next_cnt, key);
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
+  for (int k = 0; k < ITEMS; ++k) {
     const uint32_t lp = (uint32_t)(k * kSortThreads + threadIdx.x);
     if (FULL || lp < cnt) store_pay<OUT_BLOCKED>(io, L, dest[k], (inner >> k) & 1u, L.pay[lp]);
   }
   lds_barrier();  // the buffers are reused by the next tile
 }
 
-template <int RB, bool IN_BLOCKED, bool OUT_BLOCKED>
+template <int RB, bool IN_BLOCKED, bool OUT_BLOCKED, int ITEMS>
 __global__ __launch_bounds__(kSortThreads) void k_downsweep(SortPack pk, const uint32_t* __restrict__ offsets) {
-  constexpr int NB = 1 << RB;
+  constexpr int NB = 1 << RB, kTile = kSortThreads * ITEMS;
+  static_assert(NB <= kSortThreads, "one thread per digit value");
   __shared__ uint32_t s_key[kTile];
   __shared__ uint2 s_pay[kTile];
   __shared__ uint32_t s_wh[kSortWaves * NB];
@@ -533,30 +540,53 @@ __global__ __launch_bounds__(kSortThreads) void k_downsweep(SortPack pk, const u
   if (lds_tab)
     for (uint32_t b = threadIdx.x; b < n_out_blocks; b += kSortThreads) s_blk[b] = G(sg.io.out_blocks)[b];
   const SortLds L{s_key, s_pay, s_wh, s_dig, s_run, s_tmp, s_sink, lds_tab ? s_blk : nullptr};
-  for (uint32_t d = threadIdx.x; d < nd; d += kSortThreads) {
-    s_run[d] = offsets[sg.cbase + (uint64_t)d * sg.n_ranges + r] - sg.base;
+  const uint32_t dt = threadIdx.x;
+  if (pk.self_offsets) {
+    // few ranges: the raw counts (range by range), summed here -- thread d
+    // its digit's records in all ranges and in those before this one, then a
+    // scan over the digits -- instead of by a scan in launches of its own
+    uint32_t before = 0, tot = 0;
+    if (dt < nd) {
+      const NG_GLOBAL uint32_t* c = G(offsets) + sg.cbase + dt;
+#pragma unroll 16
+      for (uint32_t q = 0; q < sg.n_ranges; ++q) {
+        const uint32_t v = c[(uint64_t)q << nbits];
+        tot += v;
+        before += q < r ? v : 0u;
+      }
+    }
+    const uint32_t inc = wave_inclusive_scan(tot);
+    if ((dt & 63) == 63) s_tmp[dt >> 6] = inc;
+    lds_barrier();
+    uint32_t start = inc - tot + before;
+    for (uint32_t w = 0; w < (dt >> 6); ++w) start += s_tmp[w];
+    if (dt < nd) s_run[dt] = start;
+  } else if (dt < nd) {
+    s_run[dt] = offsets[sg.cbase + (uint64_t)dt * sg.n_ranges + r] - sg.base;
+  }
+  if (dt < nd) {
 #pragma unroll
-    for (int v = 0; v < kSortWaves; ++v) s_wh[v * NB + d] = 0;
+    for (int v = 0; v < kSortWaves; ++v) s_wh[v * NB + dt] = 0;
   }
   lds_barrier();
-  const RangeTiles rt = range_tiles(sg, r);
+  const RangeTiles rt = range_tiles<ITEMS>(sg, r);
   // the keys of each tile are loaded while the tile before it stores its
   // payloads; the payloads load at the start of their tile and are first
   // needed after the ranking
-  uint32_t key[kItems];
-  uint2 pay[kItems];
-  load_keys_any<IN_BLOCKED>(sg.io, rt.start, rt.n_full ? (uint32_t)kTile : rt.tail, key);
+  uint32_t key[ITEMS];
+  uint2 pay[ITEMS];
+  load_keys_any<IN_BLOCKED, ITEMS>(sg.io, rt.start, rt.n_full ? (uint32_t)kTile : rt.tail, key);
   for (uint32_t t = 0; t < rt.n_full; ++t) {
     const uint32_t base = rt.start + t * (uint32_t)kTile;
     const uint32_t next_cnt = t + 1 < rt.n_full ? (uint32_t)kTile : rt.tail;
-    load_pays<IN_BLOCKED, true>(sg.io, base, kTile, pay);
-    sort_tile<RB, IN_BLOCKED, OUT_BLOCKED, true>(sg.io, base, kTile, shift, nbits, L, key, pay,
+    load_pays<IN_BLOCKED, true, ITEMS>(sg.io, base, kTile, pay);
+    sort_tile<RB, IN_BLOCKED, OUT_BLOCKED, true, ITEMS>(sg.io, base, kTile, shift, nbits, L, key, pay,
                                                  base + (uint32_t)kTile, next_cnt);
   }
   if (rt.tail) {
     const uint32_t base = rt.start + rt.n_full * (uint32_t)kTile;
-    load_pays<IN_BLOCKED, false>(sg.io, base, rt.tail, pay);
-    sort_tile<RB, IN_BLOCKED, OUT_BLOCKED, false>(sg.io, base, rt.tail, shift, nbits, L, key, pay, 0, 0u);
+    load_pays<IN_BLOCKED, false, ITEMS>(sg.io, base, rt.tail, pay);
+    sort_tile<RB, IN_BLOCKED, OUT_BLOCKED, false, ITEMS>(sg.io, base, rt.tail, shift, nbits, L, key, pay, 0, 0u);
   }
 }
 
@@ -581,6 +611,11 @@ __global__ __launch_bounds__(kThreads) void k_scan_reduce(const uint32_t* __rest
   if (threadIdx.x == 0) partial[blockIdx.x] = total;
 }
 
+// A scan tile's prefix is the sum of the partials before it: summed by each
+// tile's workgroup (up to kScanSelf of them), or scanned first by one
+// workgroup (one more launch) when there are more.
+constexpr uint32_t kScanSelf = 2048;
+
 __global__ __launch_bounds__(kThreads) void k_scan_partials(uint32_t* __restrict__ partial, uint64_t nb,
                                                             uint32_t* __restrict__ total_out) {
   __shared__ uint32_t s_tmp[kWaves];
@@ -596,8 +631,10 @@ __global__ __launch_bounds__(kThreads) void k_scan_partials(uint32_t* __restrict
   if (threadIdx.x == 0 && total_out) *total_out = carry;
 }
 
+template <bool SELF>
 __global__ __launch_bounds__(kThreads) void k_scan_down(const uint32_t* in, uint32_t* out, uint64_t n,
-                                                        const uint32_t* __restrict__ partial) {
+                                                        const uint32_t* __restrict__ partial,
+                                                        uint32_t* __restrict__ total_out) {
   __shared__ uint32_t s_tmp[kWaves];
   const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
   uint32_t v[kScanItems];
@@ -608,8 +645,17 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(const uint32_t* in, uint
     v[k] = j < n ? in[j] : 0u;
     sum += v[k];
   }
+  uint32_t before;
+  if constexpr (SELF) {
+    uint32_t mine = 0;
+    for (uint32_t j = threadIdx.x; j < blockIdx.x; j += kThreads) mine += partial[j];
+    (void)block_exclusive_scan(mine, s_tmp, &before);
+  } else {
+    before = partial[blockIdx.x];
+  }
   uint32_t total;
-  uint32_t run = partial[blockIdx.x] + block_exclusive_scan(sum, s_tmp, &total);
+  uint32_t run = before + block_exclusive_scan(sum, s_tmp, &total);
+  if (SELF && total_out && threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) *total_out = before + total;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     const uint64_t j = base + k;
@@ -648,8 +694,29 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t value, uint64_t n) {
 //   write: one thread per 32-bit bitmap word; a workgroup scan of the word
 //          popcounts places every group start in order
 // ---------------------------------------------------------------------------
-constexpr int kGiItems = 32;
-constexpr int kGiTile = kThreads * kGiItems;  // 8,192 positions = 256 bitmap words
+// Positions per tile: 32 per thread of the flags kernel (8,192: 256 bitmap
+// words, four waves of the write kernel), or 8 (2,048, one wave) where large
+// tiles would leave most of the chip idle.
+constexpr int kGiItemsLarge = 32, kGiItemsSmall = 8;
+
+// Groups in tiles [t0, t1) from the per-tile counts (the whole workgroup of
+// THREADS threads calls it; s_sum holds THREADS / 64 words).
+template <int THREADS>
+__device__ __forceinline__ uint32_t gi_sum(const uint32_t* __restrict__ tile_flags, uint32_t t0, uint32_t t1,
+                                           uint32_t* s_sum) {
+  uint32_t v = 0;
+#pragma unroll 4
+  for (uint32_t t = t0 + threadIdx.x; t < t1; t += THREADS) v += G(tile_flags)[t];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  __syncthreads();  // s_sum may still be read from a call before
+  if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = v;
+  __syncthreads();
+  uint32_t sum = 0;
+#pragma unroll
+  for (int w = 0; w < THREADS / 64; ++w) sum += s_sum[w];
+  return sum;
+}
 
 __device__ __forceinline__ uint64_t group_key(char* const* __restrict__ blocks, int log2B, uint64_t j) {
   const uint64_t B = 1ull << log2B;
@@ -665,7 +732,9 @@ __device__ __forceinline__ GiSeg gi_seg(const GiPack& pk, const uint32_t* table,
   return C_struct(pk.segs, k);
 }
 
+template <int kGiItems>
 __global__ __launch_bounds__(kThreads) void k_group_flags(GiPack pk, uint32_t* __restrict__ tile_flags) {
+  constexpr int kGiTile = kThreads * kGiItems;
   __shared__ uint32_t s_tmp[kWaves];
   const GiSeg sg = gi_seg(pk, pk.seg_of_tile, blockIdx.x);
   const int log2B = pk.log2B;
@@ -748,9 +817,12 @@ __global__ __launch_bounds__(kThreads) void k_group_flags(GiPack pk, uint32_t* _
 // each. Dense groups go 64 positions at a time, the flagged lanes taking
 // consecutive group numbers: one fully coalesced round per 64 positions that
 // hold a group. A lane-by-lane round is priced at four of those.
+template <int kGiItems>
 __global__ __launch_bounds__(kThreads) void k_group_write(GiPack pk, const uint32_t* __restrict__ tile_base) {
-  static_assert(kGiTile == kWaves * 64 * 32, "one bitmap word per lane");
-  __shared__ uint32_t s_cnt[kWaves];
+  constexpr int kGiTile = kThreads * kGiItems;
+  constexpr int kGiWaves = kGiTile / (64 * 32);
+  static_assert(kGiTile == kGiWaves * 64 * 32 && kGiWaves <= kWaves, "one bitmap word per lane");
+  __shared__ uint32_t s_cnt[kGiWaves];
   const GiSeg sg = gi_seg(pk, pk.seg_of_tile, blockIdx.x);
   const uint32_t n = (uint32_t)sg.n;
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -771,7 +843,13 @@ __global__ __launch_bounds__(kThreads) void k_group_write(GiPack pk, const uint3
   }
   if (lane == 63) s_cnt[wave] = incl;
   __syncthreads();
-  uint32_t g = tile_base[blockIdx.x] - tile_base[sg.tile0];
+  uint32_t g = 0;
+  if (pk.self_prefix) {
+    __shared__ uint32_t s_sum[kGiWaves];
+    g = gi_sum<64 * kGiWaves>(tile_base, sg.tile0, blockIdx.x, s_sum);
+  } else {
+    g = tile_base[blockIdx.x] - tile_base[sg.tile0];
+  }
   for (uint32_t w = 0; w < wave; ++w) g += s_cnt[w];
   const uint64_t B = 1ull << pk.log2B;
   const char* blk = C(sg.blocks, base >> pk.log2B);  // kGiTile divides the block size
@@ -780,7 +858,7 @@ __global__ __launch_bounds__(kThreads) void k_group_write(GiPack pk, const uint3
   NG_GLOBAL uint32_t* gsrc = G(sg.group_src);
   const uint32_t p0 = base + wave * 2048u;  // first position of this wave
   const uint64_t nz = __ballot(bits != 0);
-  uint64_t chunks = (nz | (nz >> 1)) & 0x5555555555555555ull;  // bit 2i: positions 64i.. hold a group
+  const uint64_t chunks = (nz | (nz >> 1)) & 0x5555555555555555ull;  // bit 2i: positions 64i.. hold a group
   if (4u * __builtin_amdgcn_readfirstlane(mx) <= (uint32_t)__popcll(chunks)) {
     uint32_t gl = g + incl - pc;
     while (bits) {
@@ -792,17 +870,29 @@ __global__ __launch_bounds__(kThreads) void k_group_write(GiPack pk, const uint3
     }
     return;
   }
-  while (chunks) {
-    const uint32_t i = (uint32_t)(__ffsll((unsigned long long)chunks) - 1) >> 1;
-    chunks &= chunks - 1;
-    const uint32_t lo = __builtin_amdgcn_readlane(bits, 2 * i), hi = __builtin_amdgcn_readlane(bits, 2 * i + 1);
-    const uint64_t m = ((uint64_t)hi << 32) | lo;
-    if ((m >> lane) & 1ull) {
-      const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-      gstart[g + below] = p0 + 64u * i + lane;
-      gsrc[g + below] = src[64u * i + lane];
+  // eight 64-position chunks at a time, their sources loading together
+  for (uint32_t i0 = 0; i0 < 32; i0 += 8) {
+    if (((chunks >> (2 * i0)) & 0x5555u) == 0) continue;
+    uint32_t sv[8];
+#pragma unroll
+    for (uint32_t u = 0; u < 8; ++u) {
+      const uint32_t i = i0 + u;
+      const uint32_t lo = __builtin_amdgcn_readlane(bits, 2 * i), hi = __builtin_amdgcn_readlane(bits, 2 * i + 1);
+      const bool f = ((((uint64_t)hi << 32) | lo) >> lane) & 1ull;
+      sv[u] = f ? src[64u * i + lane] : 0u;
     }
-    g += (uint32_t)__popcll(m);
+#pragma unroll
+    for (uint32_t u = 0; u < 8; ++u) {
+      const uint32_t i = i0 + u;
+      const uint32_t lo = __builtin_amdgcn_readlane(bits, 2 * i), hi = __builtin_amdgcn_readlane(bits, 2 * i + 1);
+      const uint64_t m = ((uint64_t)hi << 32) | lo;
+      if ((m >> lane) & 1ull) {
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+        gstart[g + below] = p0 + 64u * i + lane;
+        gsrc[g + below] = sv[u];
+      }
+      g += (uint32_t)__popcll(m);
+    }
   }
 }
 
@@ -811,7 +901,13 @@ __global__ __launch_bounds__(kThreads) void k_group_write(GiPack pk, const uint3
 __global__ __launch_bounds__(kThreads) void k_group_ptr(GiPack pk, const uint32_t* __restrict__ tile_base) {
   const GiSeg sg = gi_seg(pk, pk.seg_of_ptr_block, blockIdx.x);
   const uint32_t lb = blockIdx.x - sg.ptr_block0;
-  const uint32_t ng = tile_base[sg.tile0 + sg.n_tiles] - tile_base[sg.tile0];  // G
+  uint32_t ng;  // G
+  if (pk.self_prefix) {
+    __shared__ uint32_t s_sum[kWaves];
+    ng = gi_sum<kThreads>(tile_base, sg.tile0, sg.tile0 + sg.n_tiles, s_sum);
+  } else {
+    ng = tile_base[sg.tile0 + sg.n_tiles] - tile_base[sg.tile0];
+  }
   if (lb == 0 && threadIdx.x == 0) {
     *G(sg.n_groups) = ng;
     G(sg.group_start)[ng] = (uint32_t)sg.n;  // group_start[G] = n closes the last group
@@ -828,28 +924,28 @@ __global__ __launch_bounds__(kThreads) void k_group_ptr(GiPack pk, const uint32_
   }
 }
 
-template <int RB>
+template <int RB, int ITEMS>
 hipError_t upsweep_rb(const SortPack& pk, uint32_t* counts, hipStream_t s) {
   const dim3 grid(8 * pk.ranges_per_xcd);
   if (pk.one.io.in_blocks)
-    hipLaunchKernelGGL((k_upsweep<RB, true>), grid, dim3(kSortThreads), 0, s, pk, counts);
+    hipLaunchKernelGGL((k_upsweep<RB, true, ITEMS>), grid, dim3(kSortThreads), 0, s, pk, counts);
   else
-    hipLaunchKernelGGL((k_upsweep<RB, false>), grid, dim3(kSortThreads), 0, s, pk, counts);
+    hipLaunchKernelGGL((k_upsweep<RB, false, ITEMS>), grid, dim3(kSortThreads), 0, s, pk, counts);
   return hipGetLastError();
 }
 
-template <int RB>
+template <int RB, int ITEMS>
 hipError_t downsweep_rb(const SortPack& pk, const uint32_t* offsets, hipStream_t s) {
   const dim3 grid(8 * pk.ranges_per_xcd);
   const bool ib = pk.one.io.in_blocks != nullptr, ob = pk.one.io.out_blocks != nullptr;
   if (ib && ob)
-    hipLaunchKernelGGL((k_downsweep<RB, true, true>), grid, dim3(kSortThreads), 0, s, pk, offsets);
+    hipLaunchKernelGGL((k_downsweep<RB, true, true, ITEMS>), grid, dim3(kSortThreads), 0, s, pk, offsets);
   else if (ib)
-    hipLaunchKernelGGL((k_downsweep<RB, true, false>), grid, dim3(kSortThreads), 0, s, pk, offsets);
+    hipLaunchKernelGGL((k_downsweep<RB, true, false, ITEMS>), grid, dim3(kSortThreads), 0, s, pk, offsets);
   else if (ob)
-    hipLaunchKernelGGL((k_downsweep<RB, false, true>), grid, dim3(kSortThreads), 0, s, pk, offsets);
+    hipLaunchKernelGGL((k_downsweep<RB, false, true, ITEMS>), grid, dim3(kSortThreads), 0, s, pk, offsets);
   else
-    hipLaunchKernelGGL((k_downsweep<RB, false, false>), grid, dim3(kSortThreads), 0, s, pk, offsets);
+    hipLaunchKernelGGL((k_downsweep<RB, false, false, ITEMS>), grid, dim3(kSortThreads), 0, s, pk, offsets);
   return hipGetLastError();
 }
 
@@ -1559,19 +1655,25 @@ hipError_t launch_generate_batch(const GenDesc* d_descs, uint32_t n_calls, uint6
   return hipGetLastError();
 }
 
-uint32_t sort_tile_size() { return kTile; }
+uint32_t sort_tile_size(bool small) { return kSortThreads * (small ? kItemsSmall : kItemsLarge); }
 int sort_max_radix_bits() { return kMaxRadixBits; }
 
 hipError_t launch_upsweep(const SortPack& pk, uint32_t* counts, hipStream_t s) {
   if (pk.total_ranges == 0) return hipSuccess;
   if (pk.max_nbits > (uint32_t)kMaxRadixBits) return hipErrorInvalidValue;
-  return pk.max_nbits <= 8 ? upsweep_rb<8>(pk, counts, s) : upsweep_rb<9>(pk, counts, s);
+  if (pk.small_tiles)
+    return pk.max_nbits <= 8 ? upsweep_rb<8, kItemsSmall>(pk, counts, s) : upsweep_rb<9, kItemsSmall>(pk, counts, s);
+  return pk.max_nbits <= 8 ? upsweep_rb<8, kItemsLarge>(pk, counts, s) : upsweep_rb<9, kItemsLarge>(pk, counts, s);
 }
 
 hipError_t launch_downsweep(const SortPack& pk, const uint32_t* offsets, hipStream_t s) {
   if (pk.total_ranges == 0) return hipSuccess;
   if (pk.max_nbits > (uint32_t)kMaxRadixBits) return hipErrorInvalidValue;
-  return pk.max_nbits <= 8 ? downsweep_rb<8>(pk, offsets, s) : downsweep_rb<9>(pk, offsets, s);
+  if (pk.small_tiles)
+    return pk.max_nbits <= 8 ? downsweep_rb<8, kItemsSmall>(pk, offsets, s)
+                             : downsweep_rb<9, kItemsSmall>(pk, offsets, s);
+  return pk.max_nbits <= 8 ? downsweep_rb<8, kItemsLarge>(pk, offsets, s)
+                           : downsweep_rb<9, kItemsLarge>(pk, offsets, s);
 }
 
 uint64_t scan_tmp_words(uint64_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
@@ -1583,9 +1685,13 @@ hipError_t launch_exclusive_scan(const uint32_t* in, uint32_t* out, uint64_t n, 
     if (total) hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, total, 0u, (uint64_t)1);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(k_scan_reduce, dim3((uint32_t)nb), dim3(kThreads), 0, s, in, n, tmp);
+  if (nb > 1) hipLaunchKernelGGL(k_scan_reduce, dim3((uint32_t)nb), dim3(kThreads), 0, s, in, n, tmp);
+  if (nb <= kScanSelf) {
+    hipLaunchKernelGGL(k_scan_down<true>, dim3((uint32_t)nb), dim3(kThreads), 0, s, in, out, n, tmp, total);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kThreads), 0, s, tmp, nb, total);
-  hipLaunchKernelGGL(k_scan_down, dim3((uint32_t)nb), dim3(kThreads), 0, s, in, out, n, tmp);
+  hipLaunchKernelGGL(k_scan_down<false>, dim3((uint32_t)nb), dim3(kThreads), 0, s, in, out, n, tmp, nullptr);
   return hipGetLastError();
 }
 
@@ -1684,7 +1790,7 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t value, uint64_t n, hipStream_t 
   return hipGetLastError();
 }
 
-uint32_t gi_tile_size() { return kGiTile; }
+uint32_t gi_tile_size(bool small) { return kThreads * (small ? kGiItemsSmall : kGiItemsLarge); }
 
 uint32_t gi_ptr_blocks(uint32_t n_nodes) {
   const uint64_t b = ((uint64_t)n_nodes + 1 + kThreads - 1) / kThreads;
@@ -1693,13 +1799,19 @@ uint32_t gi_ptr_blocks(uint32_t n_nodes) {
 
 hipError_t launch_group_flags(const GiPack& pk, uint32_t* tile_flags, hipStream_t s) {
   if (pk.total_tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_group_flags, dim3(pk.total_tiles), dim3(kThreads), 0, s, pk, tile_flags);
+  if (pk.small_tiles)
+    hipLaunchKernelGGL(k_group_flags<kGiItemsSmall>, dim3(pk.total_tiles), dim3(kThreads), 0, s, pk, tile_flags);
+  else
+    hipLaunchKernelGGL(k_group_flags<kGiItemsLarge>, dim3(pk.total_tiles), dim3(kThreads), 0, s, pk, tile_flags);
   return hipGetLastError();
 }
 
 hipError_t launch_group_write(const GiPack& pk, const uint32_t* tile_base, hipStream_t s) {
   if (pk.total_tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_group_write, dim3(pk.total_tiles), dim3(kThreads), 0, s, pk, tile_base);
+  if (pk.small_tiles)
+    hipLaunchKernelGGL(k_group_write<kGiItemsSmall>, dim3(pk.total_tiles), dim3(64), 0, s, pk, tile_base);
+  else
+    hipLaunchKernelGGL(k_group_write<kGiItemsLarge>, dim3(pk.total_tiles), dim3(kThreads), 0, s, pk, tile_base);
   return hipGetLastError();
 }
 

@@ -571,6 +571,16 @@ struct CalSeg {
   ScratchBump* sb = nullptr;  // scratch from a fixed region instead of the arena
 };
 
+// Static ranges of consecutive tiles, one workgroup each, and the tiles of
+// the group index.
+void cal_ranges(CalSeg& g, bool small) {
+  const uint64_t tile = ng::sort_tile_size(small), gi_tile = ng::gi_tile_size(small);
+  const uint64_t n_tiles = (g.N + tile - 1) / tile;
+  g.tiles_per_range = (uint32_t)std::max<uint64_t>(1, (n_tiles + g.c->sort_ranges - 1) / g.c->sort_ranges);
+  g.n_ranges = (uint32_t)((n_tiles + g.tiles_per_range - 1) / g.tiles_per_range);
+  g.gi_tiles = (g.N + gi_tile - 1) / gi_tile;
+}
+
 // Digit schedule and geometry (no allocation).
 int cal_plan(CalSeg& g) {
   ng_ctx* c = g.c;
@@ -589,12 +599,7 @@ int cal_plan(CalSeg& g) {
     g.shift[p] = (uint32_t)sh;
     sh += (int)g.nbits[p];
   }
-  // static ranges of consecutive tiles, one workgroup each
-  const uint64_t tile = ng::sort_tile_size();
-  const uint64_t n_tiles = (g.N + tile - 1) / tile;
-  g.tiles_per_range = (uint32_t)std::max<uint64_t>(1, (n_tiles + c->sort_ranges - 1) / c->sort_ranges);
-  g.n_ranges = (uint32_t)((n_tiles + g.tiles_per_range - 1) / g.tiles_per_range);
-  g.gi_tiles = (g.N + ng::gi_tile_size() - 1) / ng::gi_tile_size();
+  cal_ranges(g, ng::sort_small_tiles(g.N));
   g.gcap = std::min<uint64_t>(g.N, (uint64_t)g.nn * (uint64_t)c->max_delay) + 1;
   const uint64_t nblk = (g.N + c->B - 1) / c->B;
   if (nblk > c->tab_cap) {
@@ -694,9 +699,12 @@ int calibrate_copass(ng_ctx* c) {
   const uint32_t k = (uint32_t)((N + B - 1) / B);
   const uint64_t A = std::max<uint64_t>(1, std::min<uint64_t>(B, N));  // the largest block
   const int P = g.passes;
-  const uint64_t tile = ng::sort_tile_size();
-  const uint64_t blk_tiles = (A + tile - 1) / tile;
   // a sort of n <= A records uses ceil(tiles / ceil(tiles / sort_ranges)) <= min(sort_ranges, tiles) ranges
+  // of tiles of either size
+  const bool gi_small = ng::sort_small_tiles(N);
+  auto tiles_of = [](uint64_t n, bool small) { return (n + ng::sort_tile_size(small) - 1) / ng::sort_tile_size(small); };
+  uint64_t blk_tiles = tiles_of(A, ng::sort_small_tiles(A));
+  if (!ng::sort_small_tiles(A) && k > 1 && ng::sort_small_tiles(N % B)) blk_tiles = std::max(blk_tiles, tiles_of(N % B, true));
   const uint64_t max_ranges = std::max<uint64_t>(1, std::min<uint64_t>(c->sort_ranges, blk_tiles));
   uint32_t maxbits = 0;
   for (int p = 0; p < P; ++p) maxbits = std::max(maxbits, g.nbits[p]);
@@ -752,7 +760,8 @@ int calibrate_copass(ng_ctx* c) {
     if (int rc = sync_table(c)) return rc;
     // sort the packed records aux[0, n) into block b
     auto sort_into = [&](uint32_t b, uint32_t n) -> int {
-      const uint64_t tiles = (n + tile - 1) / tile;
+      const bool small = ng::sort_small_tiles(n);
+      const uint64_t tiles = tiles_of(n, small);
       const uint32_t tpr = (uint32_t)std::max<uint64_t>(1, (tiles + c->sort_ranges - 1) / c->sort_ranges);
       const uint32_t nr = (uint32_t)((tiles + tpr - 1) / tpr);
       for (int p = 0; p < P; ++p) {
@@ -783,9 +792,12 @@ int calibrate_copass(ng_ctx* c) {
         pk.total_ranges = nr;
         pk.ranges_per_xcd = (nr + 7) / 8;
         pk.max_nbits = sg.nbits;
+        pk.small_tiles = small;
+        pk.self_offsets = nr <= ng::kSelfRanges;
         NG_LAUNCH(c, "upsweep", ng::launch_upsweep(pk, counts, s));
-        NG_LAUNCH(c, "scan", ng::launch_exclusive_scan(counts, counts, ((uint64_t)1 << sg.nbits) * nr, scan_tmp,
-                                                        nullptr, s));
+        if (!pk.self_offsets)
+          NG_LAUNCH(c, "scan", ng::launch_exclusive_scan(counts, counts, ((uint64_t)1 << sg.nbits) * nr, scan_tmp,
+                                                          nullptr, s));
         NG_LAUNCH(c, "downsweep", ng::launch_downsweep(pk, counts, s));
       }
       return NG_OK;
@@ -931,9 +943,12 @@ int calibrate_copass(ng_ctx* c) {
     gp.total_tiles = gs.n_tiles;
     gp.total_ptr_blocks = gs.n_ptr_blocks;
     gp.log2B = c->log2B;
+    gp.small_tiles = gi_small;
+    gp.self_prefix = gs.n_tiles <= ng::kGiSelfTiles;
     NG_LAUNCH(c, "group_flags", ng::launch_group_flags(gp, tile_flags, s));
-    NG_LAUNCH(c, "scan", ng::launch_exclusive_scan(tile_flags, tile_flags, g.gi_tiles, scan_tmp,
-                                                    tile_flags + g.gi_tiles, s));
+    if (!gp.self_prefix)
+      NG_LAUNCH(c, "scan", ng::launch_exclusive_scan(tile_flags, tile_flags, g.gi_tiles, scan_tmp,
+                                                      tile_flags + g.gi_tiles, s));
     NG_LAUNCH(c, "group_write", ng::launch_group_write(gp, tile_flags, s));
     NG_LAUNCH(c, "group_ptr", ng::launch_group_ptr(gp, tile_flags, s));
     return NG_OK;
@@ -1160,6 +1175,10 @@ int calibrate_msd(CalSeg& g, const ng::MsdPlan& plan) {
 
 }  // namespace
 
+namespace {
+int calibrate_lsd(std::vector<CalSeg>& segs, const Uploader* upload, ScratchBump* sb, bool small);
+}
+
 int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, ScratchBump* sb) {
   if (n == 0) return NG_OK;
   if (!cs) return fail(NG_ERR_INVALID_ARG, "null context array");
@@ -1206,8 +1225,31 @@ int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, Scratc
         (g.c->calib_mode == NG_CALIB_RADIX_MSD || msd_pays(mp)))
       return calibrate_msd(segs[0], mp);
   }
+  // few records in all: small tiles, or large ones where the arena (or the
+  // fixed scratch) has no room for the larger count arrays of small ones
+  uint64_t records = 0;
+  for (auto& g : segs) records += g.N;
+  if (ng::sort_small_tiles(records)) {
+    const uint64_t used0 = sb ? sb->used : 0;
+    const int rc = calibrate_lsd(segs, upload, sb, true);
+    if (rc != NG_ERR_OOM && rc != NG_ERR_TOO_LARGE) return rc;
+    if (sb) {
+      sb->used = used0;
+      sb->ok = true;
+    }
+  }
+  return calibrate_lsd(segs, upload, sb, false);
+}
+
+namespace {
+
+// The LSD sort and group index of the planned segments.
+int calibrate_lsd(std::vector<CalSeg>& segs, const Uploader* upload, ScratchBump* sb, bool small) {
   ng_ctx* c0 = segs[0].c;
   const bool multi = segs.size() > 1;
+  for (auto& g : segs) {
+    if (g.N > 0) cal_ranges(g, small);
+  }
 
   // sort packs: segments with records, grouped by their number of passes
   std::map<int, std::vector<uint32_t>> packs;
@@ -1304,6 +1346,7 @@ int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, Scratc
     for (int p = 0; p < P; ++p) {
       ng::SortPack pk{};
       uint64_t cbase = 0, before = 0;
+      uint32_t most_ranges = 0;
       for (size_t i = 0; i < ks.size(); ++i) {
         ng::SortSeg sg = sort_seg(segs[ks[i]], p);
         sg.range0 = range0[i];
@@ -1312,12 +1355,15 @@ int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, Scratc
         cbase += ((uint64_t)1 << sg.nbits) * sg.n_ranges;
         before += sg.n;
         pk.max_nbits = std::max(pk.max_nbits, sg.nbits);
+        most_ranges = std::max(most_ranges, sg.n_ranges);
         if (i == 0) pk.one = sg;
         if (multi) h_segs[(size_t)p * ks.size() + i] = sg;
       }
       pk.n_segs = (uint32_t)ks.size();
       pk.total_ranges = total_ranges;
       pk.ranges_per_xcd = (total_ranges + 7) / 8;
+      pk.small_tiles = small;
+      pk.self_offsets = most_ranges <= ng::kSelfRanges;
       if (multi) {
         pk.segs = d_segs + (size_t)p * ks.size();
         pk.seg_of_range = d_sor;
@@ -1342,7 +1388,7 @@ int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, Scratc
       gp.seg_of_ptr_block = reinterpret_cast<const uint32_t*>(d_tables + toff);
       toff += align256(4 * total_ptr_blocks);
     }
-    uint32_t tile0 = 0, pb0 = 0;
+    uint32_t tile0 = 0, pb0 = 0, most_tiles = 0;
     for (size_t k = 0; k < segs.size(); ++k) {
       const CalSeg& g = segs[k];
       ng::GiSeg s{};
@@ -1366,11 +1412,14 @@ int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, Scratc
       if (k == 0) gp.one = s;
       tile0 += s.n_tiles;
       pb0 += s.n_ptr_blocks;
+      most_tiles = std::max(most_tiles, s.n_tiles);
     }
     gp.n_segs = (uint32_t)segs.size();
     gp.total_tiles = tile0;
     gp.total_ptr_blocks = pb0;
     gp.log2B = c0->log2B;
+    gp.small_tiles = small;
+    gp.self_prefix = most_tiles <= ng::kGiSelfTiles;
   }
   const ng::TabEntry* d_entries = nullptr;
   std::vector<uint32_t> synced_before;
@@ -1418,12 +1467,14 @@ int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, Scratc
     for (auto& pl : launches)
       for (int p = 0; p < pl.passes; ++p) {
         NG_LAUNCH(c0, "upsweep", ng::launch_upsweep(pl.pass[p], counts, s));
-        NG_LAUNCH(c0, "scan", ng::launch_exclusive_scan(counts, counts, pl.counts_n[p], scan_tmp, nullptr, s));
+        if (!pl.pass[p].self_offsets)
+          NG_LAUNCH(c0, "scan", ng::launch_exclusive_scan(counts, counts, pl.counts_n[p], scan_tmp, nullptr, s));
         NG_LAUNCH(c0, "downsweep", ng::launch_downsweep(pl.pass[p], counts, s));
       }
     NG_LAUNCH(c0, "group_flags", ng::launch_group_flags(gp, tile_flags, s));
-    NG_LAUNCH(c0, "scan", ng::launch_exclusive_scan(tile_flags, tile_flags, total_tiles, scan_tmp,
-                                                     tile_flags + total_tiles, s));
+    if (!gp.self_prefix)
+      NG_LAUNCH(c0, "scan", ng::launch_exclusive_scan(tile_flags, tile_flags, total_tiles, scan_tmp,
+                                                       tile_flags + total_tiles, s));
     NG_LAUNCH(c0, "group_write", ng::launch_group_write(gp, tile_flags, s));
     NG_LAUNCH(c0, "group_ptr", ng::launch_group_ptr(gp, tile_flags, s));
     if (multi) {
@@ -1465,6 +1516,7 @@ int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, Scratc
   return NG_OK;
 }
 
+}  // namespace
 
 void connect_commit(ng_ctx* c, const ng::GenDesc& d, int32_t max_delay) {
   c->next_cid++;
