@@ -1234,12 +1234,20 @@ __global__ __launch_bounds__(kAdvThreads) void k_spikes_advance(SpikeState st, u
   }
 }
 
-__global__ __launch_bounds__(256) void k_spikes_deliver(SpikeState st, float* __restrict__ input, uint32_t step) {
+// Delivery: a wave per spike-array entry, every connection an atomic addition
+// to its target's input.  These additions set the time: about 23 per ns
+// whatever their addresses (the full microcircuit's 3e5 per step take 13 of
+// its 24 us; keeping each line of the input to one XCD, spreading the targets
+// over 8 or 32 copies or one line each changed nothing, and adding parts of
+// the targets in LDS first, with every target index read once per part, was
+// slower at 1e4 to 1.5e6 additions per step).
+__device__ __forceinline__ void spikes_deliver(const SpikeState& st, float* __restrict__ input, uint32_t step,
+                                               uint32_t blocks) {
+  constexpr uint32_t kU = 4;  // connections per lane in flight
   const uint64_t B = 1ull << st.log2B;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t n_e = __builtin_amdgcn_readfirstlane(G(st.n_entries)[step & 1]);
-  const uint32_t waves = gridDim.x * 4;
-  for (uint32_t e = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)); e < n_e; e += waves) {
+  for (uint32_t e = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)); e < n_e; e += blocks * 4) {
     const uint2 en = ld_u32x2(st.entries + e);
     const uint32_t a = G(st.group_start)[en.x], b = G(st.group_start)[en.x + 1];
     const float m = (float)en.y;
@@ -1247,19 +1255,30 @@ __global__ __launch_bounds__(256) void k_spikes_deliver(SpikeState st, float* __
     // read once per entry, any other block only where the group reaches it
     const uint32_t ba = a >> st.log2B;
     const char* const blk_a = G(st.blocks)[ba];
-    for (uint32_t j = a + lane; j < b; j += 64) {
-      const char* blk = (j >> st.log2B) == ba ? blk_a : G(st.blocks)[j >> st.log2B];
-      const uint64_t o = j & (B - 1);
-      const uint32_t t = G(reinterpret_cast<const uint32_t*>(blk + 4 * B))[o];
-      const float w = G(reinterpret_cast<const float*>(blk + 8 * B))[o];
-      unsafeAtomicAdd(input + t, w * m);
+    for (uint64_t j0 = (uint64_t)a + lane; j0 < b; j0 += 64 * kU) {
+      uint32_t t[kU];
+      float w[kU];
+#pragma unroll
+      for (uint32_t u = 0; u < kU; ++u) {
+        const uint64_t j = j0 + 64 * u;
+        if (j < b) {
+          const char* blk = (j >> st.log2B) == ba ? blk_a : G(st.blocks)[j >> st.log2B];
+          const uint64_t o = j & (B - 1);
+          t[u] = G(reinterpret_cast<const uint32_t*>(blk + 4 * B))[o];
+          w[u] = G(reinterpret_cast<const float*>(blk + 8 * B))[o];
+        }
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < kU; ++u)
+        if (j0 + 64 * u < b) unsafeAtomicAdd(input + t[u], w[u] * m);
     }
   }
 }
 
-__global__ __launch_bounds__(256) void k_spikes_push(SpikeState st, const uint32_t* __restrict__ nodes,
-                                                     const uint32_t* __restrict__ mult, uint32_t n, uint32_t step) {
-  for (uint64_t k = blockIdx.x * 256ull + threadIdx.x; k < n; k += gridDim.x * 256ull) {
+__device__ __forceinline__ void spikes_push(const SpikeState& st, const uint32_t* __restrict__ nodes,
+                                            const uint32_t* __restrict__ mult, uint32_t n, uint32_t step,
+                                            uint32_t block, uint32_t blocks) {
+  for (uint64_t k = block * 256ull + threadIdx.x; k < n; k += blocks * 256ull) {
     const uint32_t i = G(nodes)[k];
     if (i >= st.n_nodes) {
       atomicOr(st.err, 4u);
@@ -1281,6 +1300,20 @@ __global__ __launch_bounds__(256) void k_spikes_push(SpikeState st, const uint32
     G(st.group)[sl] = 0;
     G(st.mult)[sl] = mult ? G(mult)[k] : 1u;
   }
+}
+
+// Delivery reads the spike array and adds to the input, the push writes the
+// queues: both only follow the advance, so they share a launch, the
+// workgroups past the delivery's pushing (a step of the full microcircuit at
+// 10 Hz: 27.5 us with a launch of its own for the push, 24 with this).
+__global__ __launch_bounds__(256) void k_spikes_deliver_push(SpikeState st, float* __restrict__ input, uint32_t step,
+                                                             const uint32_t* __restrict__ nodes,
+                                                             const uint32_t* __restrict__ mult, uint32_t n,
+                                                             uint32_t deliver_blocks) {
+  if (blockIdx.x >= deliver_blocks)
+    spikes_push(st, nodes, mult, n, step, blockIdx.x - deliver_blocks, gridDim.x - deliver_blocks);
+  else
+    spikes_deliver(st, input, step, deliver_blocks);
 }
 
 // ---------------------------------------------------------------------------
@@ -1737,15 +1770,12 @@ hipError_t launch_spikes_step(const SpikeState& st, const uint32_t* nodes, const
     hipLaunchKernelGGL(k_spikes_advance, dim3((st.n_nodes + kAdvThreads - 1) / kAdvThreads), dim3(kAdvThreads), 0, s,
                        st, step);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_spikes_deliver, dim3(2048), dim3(256), 0, s, st, input, step);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (n) {
-    hipLaunchKernelGGL(k_spikes_push, dim3(std::min<uint32_t>((n + 255) / 256, 4096u)), dim3(256), 0, s, st, nodes,
-                       mult, n, step);
-    e = hipGetLastError();
-  }
-  return e;
+  const uint32_t deliver_blocks = st.n_nodes ? 2048u : 0u, push_blocks = std::min<uint32_t>((n + 255) / 256, 4096u);
+  if (deliver_blocks + push_blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_spikes_deliver_push, dim3(deliver_blocks + push_blocks), dim3(256), 0, s, st, input, step,
+                     nodes, mult, n, deliver_blocks);
+  return hipGetLastError();
 }
 
 hipError_t launch_check_arrays(const CallArrays& a, uint64_t* out, uint32_t epoch, hipStream_t s) {
