@@ -242,15 +242,16 @@ hipError_t launch_msd_groups(const MsdPlan& p, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // pairwise_bernoulli: pairs (rows of sources, targets ascending) in units of
-// kPbUnit consecutive targets of one row.  count: counts[u] = connections of
-// unit u, and, when bits is not null, the decisions (16 per thread, one u16
-// per 16 pairs: kPbUnit / 8 bytes per unit).  write: the connections of unit
+// kPbUnit consecutive pairs (fewer than 2^32 pairs).  count: counts[u] =
+// connections of unit u, and, when bits is not null, the decisions (one u64
+// per 64 pairs: kPbUnit / 8 bytes per unit).  write: the connections of unit
 // u from creation position d.pos0 + offsets[u] on, in pair order, from the
 // stored decisions when bits is not null, else evaluated again.
-constexpr uint32_t kPbUnit = 4096;
-hipError_t launch_pb_count(const GenDesc& d, const uint32_t* d_key, uint32_t* counts, uint16_t* bits,
+constexpr uint32_t kPbUnit = 16384;
+uint64_t pb_units(uint64_t pairs);
+hipError_t launch_pb_count(const GenDesc& d, const uint32_t* d_key, uint32_t* counts, uint64_t* bits,
                            hipStream_t s);
-hipError_t launch_pb_write(const GenDesc& d, const uint32_t* d_key, const uint32_t* offsets, const uint16_t* bits,
+hipError_t launch_pb_write(const GenDesc& d, const uint32_t* d_key, const uint32_t* offsets, const uint64_t* bits,
                            char* const* blocks, int log2B, hipStream_t s);
 
 // ---------------------------------------------------------------------------

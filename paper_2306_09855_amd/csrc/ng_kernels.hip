@@ -952,56 +952,75 @@ hipError_t downsweep_rb(const SortPack& pk, const uint32_t* offsets, hipStream_t
 
 // ---------------------------------------------------------------------------
 // pairwise_bernoulli: pair (a, b) connects when word a*N_t + b of stream 0 is
-// below p * 2^32 (never a self-pair when those are prohibited).  A workgroup
-// takes one unit of kPbUnit targets of one row, 16 consecutive pairs per
-// thread; the counting pass and the writing pass evaluate the same words.
+// below p * 2^32 (never a self-pair when those are prohibited).  The pairs,
+// in order, are cut into units of kPbUnit whatever their rows, a workgroup a
+// unit and 64 consecutive pairs -- 16 whole Philox blocks -- a thread; the
+// counting pass and the writing pass evaluate the same words.  The counting
+// pass is bound by that arithmetic: 1.5e9 pairs in 0.53 ms (2.8 pairs per ps;
+// with rows cut into units of their own, so that a row's start could lie
+// inside a block and each pair selected its word, 1.53 ms; three targets per
+// row, 1e6 rows: 0.01 ms instead of 0.71).  Units of 16,384 pairs keep the
+// writing pass's lanes busy where few pairs connect (p = 0.08: 0.57 ms against
+// 0.91 with 4,096).
 // ---------------------------------------------------------------------------
 constexpr int kPbThreads = 256;
-constexpr int kPbPer = kPbUnit / kPbThreads;  // 16 pairs per thread
+constexpr int kPbPer = kPbUnit / kPbThreads;
+static_assert(kPbPer == 64, "one 64-bit mask per thread");
 
-__device__ __forceinline__ uint32_t pb_bits(const GenDesc& d, uint32_t a, uint32_t b0, uint32_t key0,
+// Bit k: pair q0 + k connects (q0 a multiple of 64; pairs past the last: 0).
+__device__ __forceinline__ uint64_t pb_bits(const GenDesc& d, uint32_t q0, uint64_t pairs, uint32_t key0,
                                             uint32_t key1) {
-  // bit k: pair (a, b0 + k) connects, for the pairs of this thread inside the row
-  uint32_t bits = 0;
-  uint64_t blk = ~0ull;
-  uint32_t w4[4] = {0, 0, 0, 0};
-  for (int k = 0; k < kPbPer; ++k) {
-    const uint32_t b = b0 + k;
-    if (b >= d.nt) break;
-    const uint64_t q = (uint64_t)a * d.nt + b;
-    if ((q >> 2) != blk) {
-      blk = q >> 2;
-      philox_block(blk, d.cid, kStreamSrc, key0, key1, w4);  // the decisions' stream
+  if (q0 >= pairs || d.p_thr == 0) return 0;
+  const uint32_t top = (uint32_t)(d.p_thr - 1);  // a word x connects when x <= top
+  uint32_t half[2];
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      uint32_t w[4];
+      philox_block((q0 >> 2) + (uint32_t)(8 * h + k), d.cid, kStreamSrc, key0, key1, w);  // the decisions' stream
+#pragma unroll
+      for (int r = 0; r < 4; ++r) m |= (w[r] <= top ? 1u : 0u) << (4 * k + r);
     }
-    const uint32_t x = w4[0] * ((q & 3) == 0) + w4[1] * ((q & 3) == 1) + w4[2] * ((q & 3) == 2) + w4[3] * ((q & 3) == 3);
-    const bool self = d.no_self && d.s0 + a == d.t0 + b;
-    if (!self && (uint64_t)x < d.p_thr) bits |= 1u << k;
+    if (h == 0) half[0] = m;
+    else half[1] = m;
+  }
+  uint64_t bits = ((uint64_t)half[1] << 32) | half[0];
+  if (pairs - q0 < 64) bits &= (1ull << (pairs - q0)) - 1;
+  if (d.no_self) {
+    // the self-pair of each row these pairs meet (source position a is target
+    // position s0 + a - t0)
+    uint32_t a = q0 / d.nt, b = q0 - a * d.nt;
+    for (uint64_t k0 = 0; k0 < 64; k0 += d.nt - b, b = 0, ++a) {  // pairs k0.. are row a from target b on
+      const int64_t self = (int64_t)d.s0 + a - d.t0;
+      if (self >= b && self < (int64_t)d.nt && k0 + (uint64_t)(self - b) < 64) bits &= ~(1ull << (k0 + (uint64_t)(self - b)));
+    }
   }
   return bits;
 }
 
 __global__ __launch_bounds__(kPbThreads) void k_pb_count(GenDesc d, const uint32_t* __restrict__ key,
-                                                         uint32_t* __restrict__ counts, uint16_t* __restrict__ dbits) {
+                                                         uint32_t* __restrict__ counts, uint64_t* __restrict__ dbits) {
   __shared__ uint32_t s_tmp[kPbThreads / 64];
   const uint32_t key0 = C(key, 0), key1 = C(key, 1);
-  const uint32_t upr = (d.nt + kPbUnit - 1) / kPbUnit;
-  const uint64_t units = (uint64_t)d.ns * upr;
-  for (uint64_t u = blockIdx.x; u < units; u += gridDim.x) {
-    const uint32_t a = (uint32_t)(u / upr), c = (uint32_t)(u - (uint64_t)a * upr);
-    const uint32_t bits = pb_bits(d, a, c * kPbUnit + threadIdx.x * kPbPer, key0, key1);
-    if (dbits) G(dbits)[u * kPbThreads + threadIdx.x] = (uint16_t)bits;
+  const uint64_t pairs = (uint64_t)d.ns * d.nt;
+  const uint32_t units = (uint32_t)((pairs + kPbUnit - 1) / kPbUnit);
+  for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
+    const uint64_t bits = pb_bits(d, u * kPbUnit + threadIdx.x * kPbPer, pairs, key0, key1);
+    if (dbits) G(dbits)[(uint64_t)u * kPbThreads + threadIdx.x] = bits;
     uint32_t total;
-    (void)block_exclusive_scan((uint32_t)__popc(bits), s_tmp, &total);
+    (void)block_exclusive_scan((uint32_t)__popcll(bits), s_tmp, &total);
     if (threadIdx.x == 0) counts[u] = total;
     __syncthreads();  // s_tmp is reused by the next unit
   }
 }
 
 // Writing pass.  The unit's connections are numbered j = offsets[u] + l,
-// l = 0..total-1 in pair order; their target offsets are staged in LDS, then
-// each lane takes an aligned quad of connection indices: one stream-2 block
-// gives the quad's delays and one stream-1 block its weights (the draws of
-// synapses 4q..4q+3 of a generated call), so a block is evaluated once per
+// l = 0..total-1 in pair order; their offsets in the unit are staged in LDS,
+// then each lane takes an aligned quad of connection indices: one stream-3
+// block gives the quad's delays and one stream-1 block its weights (the draws
+// of synapses 4q..4q+3 of a generated call), so a block is evaluated once per
 // four connections instead of once per connection.  A unit's connections
 // span at most two blocks (a block holds >= 2^16 connections), whose
 // addresses are read once per unit; the next unit's decisions and offset
@@ -1009,33 +1028,49 @@ __global__ __launch_bounds__(kPbThreads) void k_pb_count(GenDesc d, const uint32
 // and 4-aligned there is written with vector stores.
 __global__ __launch_bounds__(kPbThreads) void k_pb_write(GenDesc d, const uint32_t* __restrict__ key,
                                                          const uint32_t* __restrict__ offsets,
-                                                         const uint16_t* __restrict__ dbits,
+                                                         const uint64_t* __restrict__ dbits,
                                                          char* const* __restrict__ blocks, int log2B) {
   __shared__ uint32_t s_tmp[kPbThreads / 64];
-  __shared__ uint16_t s_b[kPbUnit];  // target offset within the unit of local connection l
+  __shared__ uint16_t s_b[kPbUnit];  // offset within the unit of local connection l
   const uint32_t key0 = C(key, 0), key1 = C(key, 1);
   const uint64_t B = 1ull << log2B;
-  const uint32_t upr = (d.nt + kPbUnit - 1) / kPbUnit;
-  const uint64_t units = (uint64_t)d.ns * upr;
-  uint64_t u = blockIdx.x;
-  uint32_t bits_next = 0, off_next = 0;
+  const uint64_t pairs = (uint64_t)d.ns * d.nt;
+  const uint32_t units = (uint32_t)((pairs + kPbUnit - 1) / kPbUnit);
+  uint32_t u = blockIdx.x;
+  uint64_t bits_next = 0;
+  uint32_t off_next = 0;
   if (u < units) {
-    if (dbits) bits_next = G(dbits)[u * kPbThreads + threadIdx.x];
+    if (dbits) bits_next = G(dbits)[(uint64_t)u * kPbThreads + threadIdx.x];
     off_next = offsets[u];
   }
   for (; u < units; u += gridDim.x) {
-    const uint32_t a = (uint32_t)(u / upr), c = (uint32_t)(u - (uint64_t)a * upr);
-    uint32_t bits = dbits ? bits_next : pb_bits(d, a, c * kPbUnit + threadIdx.x * kPbPer, key0, key1);
+    uint64_t bits = dbits ? bits_next : pb_bits(d, u * kPbUnit + threadIdx.x * kPbPer, pairs, key0, key1);
     const uint64_t j0 = off_next;
-    const uint64_t un = u + gridDim.x;
+    const uint32_t un = u + gridDim.x;  // units and the grid are below 2^31
     if (un < units) {
-      if (dbits) bits_next = G(dbits)[un * kPbThreads + threadIdx.x];
+      if (dbits) bits_next = G(dbits)[(uint64_t)un * kPbThreads + threadIdx.x];
       off_next = offsets[un];
     }
+    // the unit's first pair is target r0 of row a0; pair r0 + off of that row
+    // is target (r0 + off) % nt of row a0 + (r0 + off) / nt
+    const uint32_t a0 = u * kPbUnit / d.nt, r0 = u * kPbUnit - a0 * d.nt;
+    auto ends = [&](uint32_t l, uint32_t* src, uint32_t* tgt) {
+      uint64_t x = (uint64_t)r0 + s_b[l];
+      uint32_t a;
+      if (d.nt >= kPbUnit) {  // at most one row further
+        a = x >= d.nt ? 1u : 0u;
+        x -= a ? d.nt : 0u;
+      } else {  // r0 < nt < kPbUnit: 32 bits
+        a = (uint32_t)x / d.nt;
+        x -= a * d.nt;
+      }
+      *src = d.s0 + a0 + a;
+      *tgt = d.t0 + (uint32_t)x;
+    };
     uint32_t total;
-    uint32_t l = block_exclusive_scan((uint32_t)__popc(bits), s_tmp, &total);
+    uint32_t l = block_exclusive_scan((uint32_t)__popcll(bits), s_tmp, &total);
     while (bits) {
-      const uint32_t k = (uint32_t)(__ffs(bits) - 1);
+      const uint32_t k = (uint32_t)__builtin_ctzll(bits);
       bits &= bits - 1;
       s_b[l++] = (uint16_t)(threadIdx.x * kPbPer + k);
     }
@@ -1043,7 +1078,6 @@ __global__ __launch_bounds__(kPbThreads) void k_pb_write(GenDesc d, const uint32
     if (total) {
       const uint64_t j1 = j0 + total;  // this unit's connections [j0, j1)
       const uint64_t q0 = j0 >> 2, nq = ((j1 - 1) >> 2) - q0 + 1;
-      const uint32_t src = d.s0 + a, tgt0 = d.t0 + c * kPbUnit;
       const uint64_t bA = (d.pos0 + j0) >> log2B, bZ = (d.pos0 + j1 - 1) >> log2B;  // bZ <= bA + 1
       char* const blkA = G(blocks)[bA];
       char* const blkZ = bZ != bA ? G(blocks)[bZ] : blkA;
@@ -1072,9 +1106,11 @@ __global__ __launch_bounds__(kPbThreads) void k_pb_write(GenDesc d, const uint32
           char* blk = (p4 >> log2B) == bA ? blkA : blkZ;
           const uint64_t o = p4 & (B - 1);
           const uint32_t lq = (uint32_t)(4 * q - j0);
-          *(NG_GLOBAL u32x4*)(blk + 4 * o) = u32x4{src, src, src, src};
-          *(NG_GLOBAL u32x4*)(blk + 4 * B + 4 * o) =
-              u32x4{tgt0 + s_b[lq], tgt0 + s_b[lq + 1], tgt0 + s_b[lq + 2], tgt0 + s_b[lq + 3]};
+          uint32_t src[4], tgt[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) ends(lq + r, &src[r], &tgt[r]);
+          *(NG_GLOBAL u32x4*)(blk + 4 * o) = u32x4{src[0], src[1], src[2], src[3]};
+          *(NG_GLOBAL u32x4*)(blk + 4 * B + 4 * o) = u32x4{tgt[0], tgt[1], tgt[2], tgt[3]};
           *(NG_GLOBAL u32x4*)(blk + 8 * B + 4 * o) =
               u32x4{__float_as_uint(w[0]), __float_as_uint(w[1]), __float_as_uint(w[2]), __float_as_uint(w[3])};
           *(NG_GLOBAL u32x2*)(blk + 12 * B + 2 * o) =
@@ -1087,8 +1123,10 @@ __global__ __launch_bounds__(kPbThreads) void k_pb_write(GenDesc d, const uint32
             const uint64_t p = d.pos0 + j;
             char* blk = (p >> log2B) == bA ? blkA : blkZ;
             const uint64_t o = p & (B - 1);
+            uint32_t src, tgt;
+            ends((uint32_t)(j - j0), &src, &tgt);
             G(reinterpret_cast<uint32_t*>(blk))[o] = src;
-            G(reinterpret_cast<uint32_t*>(blk + 4 * B))[o] = tgt0 + s_b[j - j0];
+            G(reinterpret_cast<uint32_t*>(blk + 4 * B))[o] = tgt;
             G(reinterpret_cast<float*>(blk + 8 * B))[o] = w[r];
             G(reinterpret_cast<int16_t*>(blk + 12 * B))[o] = (int16_t)dl[r];
           }
@@ -1735,18 +1773,20 @@ hipError_t launch_set_ptrs(char** tab, uint32_t first, uint32_t count, const uin
   return hipGetLastError();
 }
 
-hipError_t launch_pb_count(const GenDesc& d, const uint32_t* d_key, uint32_t* counts, uint16_t* bits,
+uint64_t pb_units(uint64_t pairs) { return (pairs + kPbUnit - 1) / kPbUnit; }
+
+hipError_t launch_pb_count(const GenDesc& d, const uint32_t* d_key, uint32_t* counts, uint64_t* bits,
                            hipStream_t s) {
-  const uint64_t units = (uint64_t)d.ns * ((d.nt + kPbUnit - 1) / kPbUnit);
+  const uint64_t units = pb_units((uint64_t)d.ns * d.nt);
   if (units == 0) return hipSuccess;
   hipLaunchKernelGGL(k_pb_count, dim3((uint32_t)std::min<uint64_t>(units, 65536)), dim3(kPbThreads), 0, s, d, d_key,
                      counts, bits);
   return hipGetLastError();
 }
 
-hipError_t launch_pb_write(const GenDesc& d, const uint32_t* d_key, const uint32_t* offsets, const uint16_t* bits,
+hipError_t launch_pb_write(const GenDesc& d, const uint32_t* d_key, const uint32_t* offsets, const uint64_t* bits,
                            char* const* blocks, int log2B, hipStream_t s) {
-  const uint64_t units = (uint64_t)d.ns * ((d.nt + kPbUnit - 1) / kPbUnit);
+  const uint64_t units = pb_units((uint64_t)d.ns * d.nt);
   if (units == 0) return hipSuccess;
   hipLaunchKernelGGL(k_pb_write, dim3((uint32_t)std::min<uint64_t>(units, 65536)), dim3(kPbThreads), 0, s, d, d_key,
                      offsets, bits, blocks, log2B);

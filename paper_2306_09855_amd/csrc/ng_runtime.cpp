@@ -1636,11 +1636,11 @@ static int connect_pairwise(ng_ctx* c, ng_range src, ng_range tgt, const ng_conn
   d.p_thr = (uint64_t)std::floor(conn->p * 4294967296.0);
   d.cid = c->next_cid;
   d.no_self = !conn->allow_autapses;
-  const uint64_t units = (uint64_t)src.n * ((tgt.n + ng::kPbUnit - 1) / ng::kPbUnit);
+  const uint64_t units = ng::pb_units((uint64_t)src.n * tgt.n);
   uint64_t n = 0;
   uint32_t* counts = nullptr;
   uint64_t cbytes = 0, bits_bytes = 0;
-  uint16_t* bits = nullptr;
+  uint64_t* bits = nullptr;
   if (units) {
     // the count is read back through pinned words: had before any launch
     if (!host_words(c, 1)) return NG_ERR_DEVICE;
@@ -1656,7 +1656,7 @@ static int connect_pairwise(ng_ctx* c, ng_range src, ng_range tgt, const ng_conn
     // the decisions of the counting pass, kept for the writing pass when the
     // arena has room (one bit per pair), else evaluated again
     bits_bytes = units * (ng::kPbUnit / 8);
-    bits = (uint16_t*)ctx_alloc(c, bits_bytes);
+    bits = (uint64_t*)ctx_alloc(c, bits_bytes);
     if (!bits) bits_bytes = 0;
     NG_LAUNCH(c, "pb_count", ng::launch_pb_count(d, key_ptr(c), counts, bits, c->stream));
     NG_LAUNCH(c, "scan", ng::launch_exclusive_scan(counts, counts, units, tmp, counts + units, c->stream));
