@@ -1177,7 +1177,71 @@ int calibrate_msd(CalSeg& g, const ng::MsdPlan& plan) {
 
 namespace {
 int calibrate_lsd(std::vector<CalSeg>& segs, const Uploader* upload, ScratchBump* sb, bool small);
+
+// The queued Connect calls of the contexts on the first one's stream (one
+// block size) as one upload -- block-table entries and descriptors, each
+// naming its context's table and key -- and one generation launch.  Without
+// arena room for the upload nothing happens here: each context launches its
+// own queue.
+int flush_connects_packed(ng_ctx* const* cs, uint32_t n) {
+  ng_ctx* c0 = cs[0];
+  std::vector<ng_ctx*> with;
+  uint64_t n_entries = 0, n_descs = 0;
+  for (uint32_t i = 0; i < n; ++i)
+    if (!cs[i]->queued.empty() && cs[i]->stream == c0->stream && cs[i]->gen_quads == c0->gen_quads) {
+      with.push_back(cs[i]);
+      n_entries += cs[i]->blocks.size() - cs[i]->tab_synced;
+      n_descs += cs[i]->queued.size();
+    }
+  if (with.size() < 2) return NG_OK;
+  const uint64_t ebytes = align256(sizeof(ng::TabEntry) * n_entries), bytes = ebytes + sizeof(ng::GenDesc) * n_descs;
+  char* d = ctx_alloc(c0, bytes);
+  if (!d) return NG_OK;
+  std::vector<char> h(bytes);
+  ng::GenDesc* out = reinterpret_cast<ng::GenDesc*>(h.data() + ebytes);
+  std::vector<ng::TabEntry> entries;
+  uint64_t groups = 0, syn = 0;
+  for (ng_ctx* c : with) {
+    for (uint32_t i = c->tab_synced; i < c->blocks.size(); ++i)
+      entries.push_back(ng::TabEntry{c->d_tab[c->cur], c->blocks[i], i, 0});
+    for (const ng::GenDesc& q : c->queued) {
+      ng::GenDesc g = q;
+      g.group0 += groups;
+      syn += g.n_new;
+      memcpy(out++, &g, sizeof g);
+    }
+    groups += c->queued_groups;
+  }
+  memcpy(h.data(), entries.data(), sizeof(ng::TabEntry) * entries.size());
+  if (stage_upload(c0, d, h.data(), bytes) != NG_OK) {
+    ctx_unalloc(c0, d, bytes);
+    return c0->sticky != NG_OK ? c0->sticky : NG_OK;
+  }
+  for (ng_ctx* c : with) {
+    c->tab_synced = (uint32_t)c->blocks.size();
+    c->queued.clear();
+    c->queued_groups = 0;
+  }
+  auto launch = [&]() -> int {
+    NG_HIP(c0, ng::launch_set_entries(reinterpret_cast<const ng::TabEntry*>(d), (uint32_t)entries.size(), c0->stream),
+           "block tables");
+    NG_LAUNCH_N(c0, "generate_batch", syn,
+                ng::launch_generate_batch(reinterpret_cast<const ng::GenDesc*>(d + ebytes), (uint32_t)n_descs, groups,
+                                          c0->log2B, c0->stream, c0->gen_quads));
+    return NG_OK;
+  };
+  if (int rc = launch()) {
+    for (ng_ctx* c : with) {  // their connections are lost
+      c->sticky = c0->sticky;
+      c->sticky_msg = c0->sticky_msg;
+    }
+    return rc;
+  }
+  ctx_free(c0, d, bytes);  // stream-ordered reuse is safe
+  if (!c0->capturing) ctx_flush_frees(c0);
+  return NG_OK;
 }
+}  // namespace
 
 int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, ScratchBump* sb) {
   if (n == 0) return NG_OK;
@@ -1194,6 +1258,8 @@ int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, Scratc
       if (cs[i]->log2B != cs[0]->log2B) return fail(NG_ERR_INVALID_ARG, "contexts with different block sizes");
     }
   }
+  if (n > 1)
+    if (int rc = flush_connects_packed(cs, n)) return rc;
   // (the fixed-scratch form allocates nothing: its queued calls launch one by one)
   for (uint32_t i = 0; i < n; ++i)
     if (int rc = flush_connects(cs[i], sb == nullptr)) return rc;
@@ -2161,13 +2227,17 @@ int ng_read_timing(ng_ctx* c, ng_kernel_time* out, int capacity, int* count, int
   return NG_OK;
 }
 
-int ng_sync(ng_ctx* c) {
+// ng_sync; *n_groups = the group count of the last calibration (not null).
+// One stream-ordered copy waits for the work and brings the group count and
+// the error words.
+static int sync_read(ng_ctx* c, uint32_t* n_groups) {
   if (int rc = enter(c)) return rc;
   if (int rc = not_capturing(c)) return rc;
   if (int rc = flush_connects(c)) return rc;
-  NG_HIP(c, hipStreamSynchronize(c->stream), "kernel execution");
-  uint32_t words[2] = {0, 0};
-  NG_HIP(c, hipMemcpy(words, c->d_scalars + 2, 8, hipMemcpyDeviceToHost), "read error words");
+  uint32_t all[4] = {0, 0, 0, 0};
+  NG_HIP(c, hipMemcpyWithStream(all, c->d_scalars, sizeof all, hipMemcpyDeviceToHost, c->stream), "kernel execution");
+  if (n_groups) *n_groups = all[0];
+  const uint32_t* words = all + 2;
   if (words[1]) {  // generation: the connections of some call are not valid
     c->sticky = NG_ERR_DEVICE;
     c->sticky_msg = std::string("generation error:") +
@@ -2184,9 +2254,12 @@ int ng_sync(ng_ctx* c) {
   return NG_OK;
 }
 
+int ng_sync(ng_ctx* c) { return sync_read(c, nullptr); }
+
 int ng_get_connections(ng_ctx* c, ng_conn_view* out) {
   if (!out) return fail(NG_ERR_INVALID_ARG, "null view");
-  if (int rc = ng_sync(c)) return rc;
+  uint32_t G = 0;
+  if (int rc = sync_read(c, &G)) return rc;
   memset(out, 0, sizeof *out);
   out->n_conns = c->n_conns;
   out->block_size = c->B;
@@ -2195,8 +2268,6 @@ int ng_get_connections(ng_ctx* c, ng_conn_view* out) {
   out->block_base = (void* const*)c->blocks.data();
   out->calibrated = c->calibrated ? 1 : 0;
   if (c->calibrated) {
-    uint32_t G = 0;
-    NG_HIP(c, hipMemcpy(&G, c->d_scalars, 4, hipMemcpyDeviceToHost), "read G");
     out->n_groups = G;
     out->group_ptr = c->d_group_ptr;
     out->group_start = c->d_group_start;
@@ -2228,10 +2299,9 @@ int ng_copy_connections(ng_ctx* c, uint64_t first, uint64_t count, uint32_t* src
 }
 
 int ng_copy_group_index(ng_ctx* c, uint32_t* group_ptr, uint32_t* group_start) {
-  if (int rc = ng_sync(c)) return rc;
-  if (!c->calibrated) return fail(NG_ERR_STATE, "not calibrated");
   uint32_t G = 0;
-  NG_HIP(c, hipMemcpy(&G, c->d_scalars, 4, hipMemcpyDeviceToHost), "read G");
+  if (int rc = sync_read(c, &G)) return rc;
+  if (!c->calibrated) return fail(NG_ERR_STATE, "not calibrated");
   if (group_ptr)
     NG_HIP(c, hipMemcpy(group_ptr, c->d_group_ptr, 4 * (c->gi_nodes + 1ull), hipMemcpyDefault), "copy");
   if (group_start)

@@ -286,15 +286,21 @@ def ng_connect(ctx, src: ng_range, tgt: ng_range, conn: ng_conn_spec, syn: ng_sy
     return int(cid.value), int(first.value), int(n.value)
 
 
+def _structs(kind, items):
+    """C array of structures: the bytes of structures of this kind joined (a
+    quarter of the time of the array's constructor, which takes them one by
+    one and anything else the C structure can be made from)."""
+    if set(map(type, items)) != {kind}:
+        return (kind * len(items))(*items)
+    return (kind * len(items)).from_buffer_copy(b"".join(items))
+
+
 def ng_connect_batch(ctx, srcs, tgts, conns, syns):
     n = len(srcs)
-    S = (ng_range * n)(*srcs)
-    T = (ng_range * n)(*tgts)
-    C = (ng_conn_spec * n)(*conns)
-    Y = (ng_syn_spec * n)(*syns)
     first = (ctypes.c_uint64 * n)()
-    _check(lib().ng_connect_batch(ctx, n, S, T, C, Y, first))
-    return [int(v) for v in first]
+    _check(lib().ng_connect_batch(ctx, n, _structs(ng_range, srcs), _structs(ng_range, tgts),
+                                  _structs(ng_conn_spec, conns), _structs(ng_syn_spec, syns), first))
+    return list(first)
 
 
 def ng_calibrate(ctx) -> None:
