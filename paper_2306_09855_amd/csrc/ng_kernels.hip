@@ -1533,7 +1533,176 @@ __device__ __forceinline__ uint32_t part_count(const BlockView& v, uint32_t st, 
   return a + (uint32_t)__popcll(__ballot(in && (le ? x <= t : x < t)));
 }
 
-// The partition search of the appendix.  Brackets [lo_i, hi_i]: lo_i counts
+// The partition of up to kPartMaxSub subarrays: m_i = how many of the m
+// smallest records, ordered by (key, subarray, position), lie in subarray i --
+// the same unique sizes that the bisection below finds.  V, the m-th smallest
+// key, lies in [vlo, vhi]; bracket [lo_i, hi_i) holds subarray i's records with
+// keys in that range.  Each round reads up to S evenly spaced keys of every
+// bracket into LDS, all loads in flight at once.  For any x these samples bound
+// the number of keys <= x of a subarray from both sides (the positions of the
+// last sample <= x and of the first one > x): V > x if the upper bounds sum
+// below m, V <= x if the lower ones reach m.  The two ends of what the samples
+// leave open are found by 9-way searches of the key range in LDS, eight waves
+// each, a lane per subarray.  Brackets shrink to a few sample spacings per
+// round; where they do not (long runs of equal keys), an exact count of the
+// middle key halves the key range.  With V known, exact counts of the keys < V
+// and <= V, and the keys equal to V go left in ascending i.
+// A partition is a chain of dependent reads on one compute unit: their number
+// and latency set its time.  Bisection by one trial key at a time goes through
+// some 22 rounds of ten dependent reads for 18 blocks of 2^22 records (170 us);
+// @@
+constexpr uint32_t kPartMaxSub = 512;
+constexpr uint32_t kPartKeys = 16384 + kPartMaxSub;  // sampled keys in LDS
+constexpr uint32_t kPartMaxSteps = 64;               // each round shrinks the brackets 4-fold or halves the key range
+
+__device__ __forceinline__ uint32_t part_pos(uint32_t lo, uint32_t hi, uint32_t q, uint32_t j) {
+  const uint32_t w = hi - lo;
+  return lo + (w <= (1u << q) ? j : (uint32_t)(((uint64_t)w * (2 * j + 1)) >> (q + 1)));
+}
+
+// Bounds on the number of keys <= x of subarray i (samples at s_key + i (S + 1):
+// lanes of neighbouring subarrays read different banks).
+__device__ __forceinline__ void part_bounds(const uint32_t* s_key, uint32_t lo, uint32_t hi, uint32_t q, uint32_t i,
+                                            uint32_t x, uint32_t& l, uint32_t& u) {
+  const uint32_t S = 1u << q, n = min(hi - lo, S);
+  const uint32_t* key = s_key + i * (S + 1);
+  uint32_t c = 0;
+  for (uint32_t st = S; st > 0; st >>= 1) {
+    const uint32_t z = c + st;
+    if (z <= n && key[z - 1] <= x) c = z;
+  }
+  l = c > 0 ? part_pos(lo, hi, q, c - 1) + 1 : lo;
+  u = c < n ? part_pos(lo, hi, q, c) : hi;
+}
+
+// Keys x_t = a + floor((b - a)(t + 1) / 9), t < 8; f: the first t whose key is
+// at or past the sought one (8: none); b itself is.
+__device__ __forceinline__ uint32_t part_probe(uint32_t a, uint32_t b, uint32_t t) {
+  return a + (uint32_t)((uint64_t)(b - a) * (t + 1) / 9);
+}
+__device__ __forceinline__ void part_narrow(uint32_t& a, uint32_t& b, uint32_t f) {
+  const uint32_t na = f > 0 ? part_probe(a, b, f - 1) + 1 : a;
+  if (f < 8) b = part_probe(a, b, f);
+  a = na;
+}
+
+__global__ __launch_bounds__(kPartThreads) void k_copass_partition_samples(CopassPart p) {
+  __shared__ uint32_t s_key[kPartKeys];
+  __shared__ uint32_t s_start[kPartMaxSub], s_lo[kPartMaxSub], s_hi[kPartMaxSub], s_c[kPartMaxSub];
+  __shared__ uint64_t red[kPartWaves];
+  __shared__ uint32_t s_flag[2][kPartWaves];
+  __shared__ uint32_t s_min, s_max;
+  const uint32_t k = p.k, m = p.m, tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t q = 9;  // S = 2^q samples per subarray: 512 to 32
+  while ((k << q) > kPartKeys - kPartMaxSub) --q;
+  const uint32_t S = 1u << q;
+  if (tid == 0) {
+    s_min = ~0u;
+    s_max = 0;
+  }
+  __syncthreads();
+  const uint32_t mine = tid < k ? p.len[tid] : 0u;
+  if (tid < k) {
+    const uint32_t st = p.start[tid];
+    s_start[tid] = st;
+    s_lo[tid] = 0;
+    s_hi[tid] = mine;
+    if (mine) {
+      atomicMin(&s_min, view_key(p.v, st));
+      atomicMax(&s_max, view_key(p.v, st + mine - 1));
+    }
+  }
+  uint64_t open = part_sum(mine, red);  // records in the brackets
+  uint32_t vlo = s_min, vhi = s_max, steps = 0, err = 0;
+  while (vlo < vhi) {
+    if (++steps > kPartMaxSteps) {
+      err = 1;
+      break;
+    }
+    for (uint32_t t = tid; t < (k << q); t += kPartThreads) {
+      const uint32_t i = t >> q, j = t & (S - 1), lo = s_lo[i], hi = s_hi[i];
+      if (j < min(hi - lo, S)) s_key[i * (S + 1) + j] = view_key(p.v, s_start[i] + part_pos(lo, hi, q, j));
+    }
+    __syncthreads();
+    // smallest key whose upper bounds (waves 0-7) and lower bounds (8-15) reach m
+    uint32_t a0 = vlo, b0 = vhi, a1 = vlo, b1 = vhi, par = 0;
+    while (a0 < b0 || a1 < b1) {
+      const uint32_t x = wave < 8 ? part_probe(a0, b0, wave) : part_probe(a1, b1, wave - 8);
+      uint32_t sum = 0;  // at most the records of the context
+      for (uint32_t i = lane; i < k; i += 64) {
+        uint32_t l, u;
+        part_bounds(s_key, s_lo[i], s_hi[i], q, i, x, l, u);
+        sum += wave < 8 ? u : l;
+      }
+      sum = wave_inclusive_scan(sum);
+      if (lane == 63) s_flag[par][wave] = sum >= m ? 1u : 0u;
+      __syncthreads();
+      const uint32_t f = (uint32_t)__ballot(lane < (uint32_t)kPartWaves && s_flag[par][lane & (kPartWaves - 1)] != 0);
+      part_narrow(a0, b0, (uint32_t)__ffs((f & 0xFFu) | 0x100u) - 1);
+      part_narrow(a1, b1, (uint32_t)__ffs((f >> 8) | 0x100u) - 1);
+      par ^= 1;
+    }
+    uint32_t nlo = 0, nhi = 0;
+    if (tid < k) {
+      uint32_t l, u;
+      nlo = s_lo[tid];
+      nhi = s_hi[tid];
+      if (a0 > vlo) {
+        part_bounds(s_key, s_lo[tid], s_hi[tid], q, tid, a0 - 1, l, u);
+        nlo = l;
+      }
+      if (a1 < vhi) {
+        part_bounds(s_key, s_lo[tid], s_hi[tid], q, tid, a1, l, u);
+        nhi = u;
+      }
+      s_lo[tid] = nlo;
+      s_hi[tid] = nhi;
+    }
+    vlo = a0;
+    vhi = a1;
+    uint64_t left = part_sum(nhi - nlo, red);
+    if (vlo < vhi && left > open / 4) {
+      const uint32_t t = vlo + (vhi - vlo) / 2;
+      for (uint32_t i = wave; i < k; i += kPartWaves) {
+        const uint32_t c = part_count(p.v, s_start[i], s_lo[i], s_hi[i], t, true);
+        if (lane == 0) s_c[i] = c;
+      }
+      __syncthreads();
+      const uint32_t c = tid < k ? s_c[tid] : 0u;
+      const bool past = part_sum(c, red) >= m;
+      if (past) vhi = t;
+      else vlo = t + 1;
+      if (tid < k) {
+        if (past) s_hi[tid] = nhi = c;
+        else s_lo[tid] = nlo = c;
+      }
+      left = part_sum(nhi - nlo, red);
+    }
+    open = left;
+  }
+  __syncthreads();
+  // V = vlo: the keys < V go left, and of those equal to V the first d by subarray
+  for (uint32_t i = wave; i < k; i += kPartWaves) {
+    const uint32_t le = part_count(p.v, s_start[i], s_lo[i], s_hi[i], vlo, true);
+    const uint32_t lt = part_count(p.v, s_start[i], s_lo[i], le, vlo, false);
+    if (lane == 0) {
+      s_c[i] = le;
+      s_lo[i] = lt;  // this wave alone reads bracket i
+    }
+  }
+  __syncthreads();
+  const uint32_t lt = tid < k ? s_lo[tid] : 0u, eq = tid < k ? s_c[tid] - lt : 0u;
+  const uint64_t d = m - part_sum(lt, red), pre = part_excl(eq, red);
+  if (tid < k) p.m_out[tid] = lt + (uint32_t)(pre >= d ? 0 : (d - pre < eq ? d - pre : eq));
+  if (tid == 0) {
+    p.status[0] = 1;
+    p.status[1] = steps;
+    p.status[2] = err;
+  }
+}
+
+// The partition search of the appendix, for more subarrays.  Brackets [lo_i, hi_i]: lo_i counts
 // the keys <= the lower threshold, hi_i those < the upper one.  Each round
 // bisects the widest bracket (lowest i on ties), takes its middle key as the
 // trial threshold t and counts every subarray's keys < t and <= t; if m lies
@@ -1842,7 +2011,12 @@ hipError_t launch_copass_copy(const BlockView& v, const CopyList& l, bool to_pac
 }
 
 hipError_t launch_copass_partition(const CopassPart& p, hipStream_t s) {
-  hipLaunchKernelGGL(k_copass_partition, dim3(1), dim3(kPartThreads), 0, s, p);
+  // up to kPartMaxSub subarrays the sampled search (32 samples of each fit in
+  // LDS), above the bisection
+  if (p.k <= kPartMaxSub)
+    hipLaunchKernelGGL(k_copass_partition_samples, dim3(1), dim3(kPartThreads), 0, s, p);
+  else
+    hipLaunchKernelGGL(k_copass_partition, dim3(1), dim3(kPartThreads), 0, s, p);
   return hipGetLastError();
 }
 
