@@ -1550,7 +1550,8 @@ __device__ __forceinline__ uint32_t part_count(const BlockView& v, uint32_t st, 
 // A partition is a chain of dependent reads on one compute unit: their number
 // and latency set its time.  Bisection by one trial key at a time goes through
 // some 22 rounds of ten dependent reads for 18 blocks of 2^22 records (170 us);
-// @@
+// this form through three or four rounds of one read and a few LDS searches each: 55 us
+// (512 samples 74 us, 128 56: fewer rounds, longer searches).
 constexpr uint32_t kPartMaxSub = 512;
 constexpr uint32_t kPartKeys = 16384 + kPartMaxSub;  // sampled keys in LDS
 constexpr uint32_t kPartMaxSteps = 64;               // each round shrinks the brackets 4-fold or halves the key range
@@ -1594,7 +1595,7 @@ __global__ __launch_bounds__(kPartThreads) void k_copass_partition_samples(Copas
   __shared__ uint32_t s_min, s_max;
   const uint32_t k = p.k, m = p.m, tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  uint32_t q = 9;  // S = 2^q samples per subarray: 512 to 32
+  uint32_t q = 6;  // S = 2^q samples per subarray: 64, or 32 from 257 subarrays on
   while ((k << q) > kPartKeys - kPartMaxSub) --q;
   const uint32_t S = 1u << q;
   if (tid == 0) {

@@ -1,6 +1,6 @@
 """GPU parity of the COPASS partition search at its dispatch edges: 32, 64,
-128, 256 and 512 subarrays and one more (512 samples of each down to 32, one to
-eight subarrays per lane, the bisection from 513 on), with a ragged last block,
+128, 256 and 512 subarrays and one more (one to eight subarrays per lane, 64
+samples of each up to 256, the bisection from 513 on), with a ragged last block,
 blocks whose sources do not overlap, blocks that hold every source, and keys
 shared by many thousand connections (exact counts where samples do not
 narrow).  The COPASS arrays must be those of the LSD radix form bit for bit."""
