@@ -593,21 +593,48 @@ __global__ __launch_bounds__(kSortThreads) void k_downsweep(SortPack pk, const u
 // ---------------------------------------------------------------------------
 // Device-wide exclusive scan (reduce, scan of partials, downsweep)
 // ---------------------------------------------------------------------------
-constexpr int kScanItems = 16;
-constexpr int kScanTile = kThreads * kScanItems;
+// A scan is short (2^18 counts for a block of 2^22 records) and its chain of
+// loads sets its time: one 16-byte load per thread, 1,024 threads a tile
+// (2^18 counts, both launches: 7.8 us; 16 single words per thread in 256
+// threads 12.0 us).
+constexpr int kScanThreads = 1024;
+constexpr int kScanWaves = kScanThreads / 64;
+constexpr int kScanItems = 4;
+constexpr int kScanTile = kScanThreads * kScanItems;
 
-__global__ __launch_bounds__(kThreads) void k_scan_reduce(const uint32_t* __restrict__ in, uint64_t n,
-                                                          uint32_t* __restrict__ partial) {
-  __shared__ uint32_t s_tmp[kWaves];
-  const uint64_t base = (uint64_t)blockIdx.x * kScanTile;
-  uint32_t sum = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint64_t j = base + k * kThreads + threadIdx.x;
-    if (j < n) sum += in[j];
+// Words j..j+3 of p (zeros from n on); as one load where p is 16-byte aligned.
+__device__ __forceinline__ uint4 scan_load(const uint32_t* p, uint64_t j, uint64_t n) {
+  if (((uintptr_t)p & 15) == 0 && j + 4 <= n) {
+    const u32x4 x = *(const NG_GLOBAL u32x4*)(const void*)(p + j);
+    return make_uint4(x.x, x.y, x.z, x.w);
   }
+  return make_uint4(j < n ? p[j] : 0u, j + 1 < n ? p[j + 1] : 0u, j + 2 < n ? p[j + 2] : 0u, j + 3 < n ? p[j + 3] : 0u);
+}
+
+// Exclusive scan over the kScanThreads threads; s_tmp holds kScanWaves words.
+__device__ __forceinline__ uint32_t scan_threads(uint32_t v, uint32_t* s_tmp, uint32_t* total) {
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t inc = wave_inclusive_scan(v);
+  __syncthreads();  // s_tmp of the scan before was read
+  if (lane == 63) s_tmp[wave] = inc;
+  __syncthreads();
+  uint32_t off = 0, sum = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < (uint32_t)kScanWaves; ++w) {
+    const uint32_t t = s_tmp[w];
+    off += w < wave ? t : 0u;
+    sum += t;
+  }
+  *total = sum;
+  return off + inc - v;
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* __restrict__ in, uint64_t n,
+                                                              uint32_t* __restrict__ partial) {
+  __shared__ uint32_t s_tmp[kScanWaves];
+  const uint4 v = scan_load(in, (uint64_t)blockIdx.x * kScanTile + threadIdx.x * kScanItems, n);
   uint32_t total;
-  block_exclusive_scan(sum, s_tmp, &total);
+  (void)scan_threads(v.x + v.y + v.z + v.w, s_tmp, &total);
   if (threadIdx.x == 0) partial[blockIdx.x] = total;
 }
 
@@ -632,35 +659,31 @@ __global__ __launch_bounds__(kThreads) void k_scan_partials(uint32_t* __restrict
 }
 
 template <bool SELF>
-__global__ __launch_bounds__(kThreads) void k_scan_down(const uint32_t* in, uint32_t* out, uint64_t n,
-                                                        const uint32_t* __restrict__ partial,
-                                                        uint32_t* __restrict__ total_out) {
-  __shared__ uint32_t s_tmp[kWaves];
-  const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
-  uint32_t v[kScanItems];
-  uint32_t sum = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint64_t j = base + k;
-    v[k] = j < n ? in[j] : 0u;
-    sum += v[k];
-  }
+__global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* in, uint32_t* out, uint64_t n,
+                                                            const uint32_t* __restrict__ partial,
+                                                            uint32_t* __restrict__ total_out) {
+  __shared__ uint32_t s_tmp[kScanWaves];
+  const uint64_t j = (uint64_t)blockIdx.x * kScanTile + threadIdx.x * kScanItems;
+  const uint4 v = scan_load(in, j, n);
   uint32_t before;
   if constexpr (SELF) {
     uint32_t mine = 0;
-    for (uint32_t j = threadIdx.x; j < blockIdx.x; j += kThreads) mine += partial[j];
-    (void)block_exclusive_scan(mine, s_tmp, &before);
+    for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kScanThreads) mine += partial[i];
+    (void)scan_threads(mine, s_tmp, &before);
   } else {
     before = partial[blockIdx.x];
   }
   uint32_t total;
-  uint32_t run = before + block_exclusive_scan(sum, s_tmp, &total);
+  const uint32_t r0 = before + scan_threads(v.x + v.y + v.z + v.w, s_tmp, &total);
   if (SELF && total_out && threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) *total_out = before + total;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint64_t j = base + k;
-    if (j < n) out[j] = run;
-    run += v[k];
+  const uint32_t r1 = r0 + v.x, r2 = r1 + v.y, r3 = r2 + v.z;
+  if (((uintptr_t)out & 15) == 0 && j + 4 <= n) {
+    st_u32x4(out + j, r0, r1, r2, r3);
+  } else {
+    if (j < n) out[j] = r0;
+    if (j + 1 < n) out[j + 1] = r1;
+    if (j + 2 < n) out[j + 2] = r2;
+    if (j + 3 < n) out[j + 3] = r3;
   }
 }
 
@@ -1926,13 +1949,13 @@ hipError_t launch_exclusive_scan(const uint32_t* in, uint32_t* out, uint64_t n, 
     if (total) hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, total, 0u, (uint64_t)1);
     return hipGetLastError();
   }
-  if (nb > 1) hipLaunchKernelGGL(k_scan_reduce, dim3((uint32_t)nb), dim3(kThreads), 0, s, in, n, tmp);
+  if (nb > 1) hipLaunchKernelGGL(k_scan_reduce, dim3((uint32_t)nb), dim3(kScanThreads), 0, s, in, n, tmp);
   if (nb <= kScanSelf) {
-    hipLaunchKernelGGL(k_scan_down<true>, dim3((uint32_t)nb), dim3(kThreads), 0, s, in, out, n, tmp, total);
+    hipLaunchKernelGGL(k_scan_down<true>, dim3((uint32_t)nb), dim3(kScanThreads), 0, s, in, out, n, tmp, total);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kThreads), 0, s, tmp, nb, total);
-  hipLaunchKernelGGL(k_scan_down<false>, dim3((uint32_t)nb), dim3(kThreads), 0, s, in, out, n, tmp, nullptr);
+  hipLaunchKernelGGL(k_scan_down<false>, dim3((uint32_t)nb), dim3(kScanThreads), 0, s, in, out, n, tmp, nullptr);
   return hipGetLastError();
 }
 
