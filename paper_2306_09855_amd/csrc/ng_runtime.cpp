@@ -758,8 +758,9 @@ int calibrate_copass(ng_ctx* c) {
 
   auto run = [&]() -> int {
     if (int rc = sync_table(c)) return rc;
-    // sort the packed records aux[0, n) into block b
-    auto sort_into = [&](uint32_t b, uint32_t n) -> int {
+    // sort the n packed records of the auxiliary array, or the block's own,
+    // into block b
+    auto sort_into = [&](uint32_t b, uint32_t n, bool from_block) -> int {
       const bool small = ng::sort_small_tiles(n);
       const uint64_t tiles = tiles_of(n, small);
       const uint32_t tpr = (uint32_t)std::max<uint64_t>(1, (tiles + c->sort_ranges - 1) / c->sort_ranges);
@@ -768,7 +769,9 @@ int calibrate_copass(ng_ctx* c) {
         ng::SortSeg sg{};
         sg.io.log2B = c->log2B;
         sg.io.dbits = (uint32_t)g.dbits;
-        if (p == 0) {
+        if (p == 0 && from_block) {
+          sg.io.in_blocks = tab + b;
+        } else if (p == 0) {
           sg.io.in_keys = aux_k;
           sg.io.in_pay = aux_p;
         } else {
@@ -807,15 +810,19 @@ int calibrate_copass(ng_ctx* c) {
       return (uint32_t)std::min<uint64_t>(B, N - a);
     };
     std::vector<ng::CopySeg> lists;
-    // (B) every block sorted: packed into the auxiliary array, sorted back
-    for (uint32_t b = 0; b < k; ++b) lists.push_back(ng::CopySeg{(uint32_t)((uint64_t)b * B), 0, block_len(b), 0});
-    if (k) {
+    // (B) every block sorted.  With two passes or more the first reads the
+    // block itself and the last writes it back (packing it first: 22 us more
+    // per block of 2^22); a single pass cannot read what it overwrites, so
+    // the block is packed into the auxiliary array first.
+    if (P == 1 && k) {
+      for (uint32_t b = 0; b < k; ++b) lists.push_back(ng::CopySeg{(uint32_t)((uint64_t)b * B), 0, block_len(b), 0});
       if (int rc = stage_upload(c, d_lists, lists.data(), sizeof(ng::CopySeg) * lists.size())) return rc;
     }
     for (uint32_t b = 0; b < k; ++b) {
-      NG_LAUNCH_N(c, "copass_copy", block_len(b),
-                  ng::launch_copass_copy(view, ng::CopyList{d_lists + b, 1, block_len(b)}, true, aux_k, aux_p, s));
-      if (int rc = sort_into(b, block_len(b))) return rc;
+      if (P == 1)
+        NG_LAUNCH_N(c, "copass_copy", block_len(b),
+                    ng::launch_copass_copy(view, ng::CopyList{d_lists + b, 1, block_len(b)}, true, aux_k, aux_p, s));
+      if (int rc = sort_into(b, block_len(b), P > 1)) return rc;
     }
     // the remaining region holds k sorted subarrays; block b = 0, 1, ... is
     // extracted in turn
@@ -919,7 +926,7 @@ int calibrate_copass(ng_ctx* c) {
                                            s_k[0], s_p[0], s));
       }
       // (F) the auxiliary array sorted into block b
-      if (int rc = sort_into(b, m)) return rc;
+      if (int rc = sort_into(b, m, false)) return rc;
       start = nstart;
       len = nlen;
     }

@@ -20,13 +20,22 @@ from paper_2306_09855_amd.network import Network, arena_bytes_for  # noqa: E402
 B = 1 << 16
 
 
-def _run(wl, mode):
+def _run(wl, mode, radix_bits=9):
     with Network(wl.seed, wl.h, B, arena_bytes_for(wl.n_syn, wl.n_nodes, wl.max_delay, B)) as net:
         net.set_calibration(mode)
+        net.tune(radix_bits, 1024)
         net.build(wl)
         out = net.fetch(device=True)
         gp, gs = net.group_index()
     return out, gp, gs
+
+
+def _same(x, y):
+    (a, gpa, gsa), (b, gpb, gsb) = x, y
+    for key in ("src", "tgt", "delay"):
+        assert torch.equal(a[key], b[key]), key
+    assert torch.equal(a["w"].view(torch.int32), b["w"].view(torch.int32))
+    assert np.array_equal(gpa, gpb) and np.array_equal(gsa, gsb)
 
 
 @pytest.mark.parametrize("blocks", [2, 32, 33, 64, 65, 128, 129, 256, 257, 512, 513])
@@ -46,9 +55,15 @@ def test_partition_search_sizes(blocks):
     calls.append(W.Call("fixed_total_number", (0, 3000), (5000, 3000), rest, w, ("uniform_int", 1, 3)))
     wl = W.Workload("copass_search", 41 + blocks, pops, calls)
     assert -(-wl.n_syn // B) == blocks
-    a, gpa, gsa = _run(wl, "copass")
-    b, gpb, gsb = _run(wl, "lsd")
-    for key in ("src", "tgt", "delay"):
-        assert torch.equal(a[key], b[key]), key
-    assert torch.equal(a["w"].view(torch.int32), b["w"].view(torch.int32))
-    assert np.array_equal(gpa, gpb) and np.array_equal(gsa, gsb)
+    _same(_run(wl, "copass"), _run(wl, "lsd"))
+
+
+@pytest.mark.parametrize("nodes,radix_bits", [(20, 9), (20, 4), (20, 5), (9000, 6), (9000, 4)])
+def test_block_sort_passes(nodes, radix_bits):
+    # 8-bit keys in one and two passes, 17-bit keys in three and five: a block
+    # is sorted from itself unless one pass has to do
+    n = 3 * B + 77
+    wl = W.Workload("copass_passes", 5, [nodes],
+                    [W.Call("fixed_total_number", (0, nodes), (0, nodes), n, ("normal", 0.5, 0.05),
+                            ("uniform_int", 1, 7))])
+    _same(_run(wl, "copass", radix_bits), _run(wl, "lsd"))
