@@ -79,6 +79,7 @@ struct SortIO {
   uint2* out_pay;
   int log2B;
   uint32_t dbits;           // key = src << dbits | delay
+  uint32_t key_base;        // blocked output: added to the sorted keys (records sorted by key - key_base)
 };
 
 // One segment of a digit pass.  A segment is one context's independent sort;
@@ -314,6 +315,7 @@ struct CopyList {
   const CopySeg* segs;  // device array, pre ascending
   uint32_t n_segs;
   uint32_t total;       // sum of len
+  uint32_t key_base;    // to packed: taken from each key (all are at least this)
 };
 // Copies the listed records between the block array and packed arrays
 // (key u32, payload = (tgt, weight bits)); to_packed: block array -> packed.
@@ -324,7 +326,8 @@ hipError_t launch_copass_copy(const BlockView& v, const CopyList& l, bool to_pac
 // m_out[i] = size of the left partition of subarray i.  lo, hi, mu_lo, mu_hi:
 // k words of scratch each.  status[0] = last step taken (1 threshold found,
 // 2 brackets of width one), status[1] = iterations, status[2] = 1 if the
-// iteration bound was hit.  One workgroup.
+// iteration bound was hit, status[3] = the largest key of the left partitions
+// (~0: not known).  One workgroup.
 struct CopassPart {
   BlockView v;
   const uint32_t* start;

@@ -488,9 +488,10 @@ __device__ __forceinline__ void sort_tile(const SortIO& io, uint64_t base, uint3
       if constexpr (OUT_BLOCKED) {
         char* blk = out_block(io, L, dest[k]);
         const uint64_t o = dest[k] & (B - 1);
-        if (in) st_u32_nt(blk + 4 * o, kk >> io.dbits);
-        else G(reinterpret_cast<uint32_t*>(blk))[o] = kk >> io.dbits;
-        G(reinterpret_cast<int16_t*>(blk + 12 * B))[o] = (int16_t)(kk & dmask);
+        const uint32_t full = kk + io.key_base;
+        if (in) st_u32_nt(blk + 4 * o, full >> io.dbits);
+        else G(reinterpret_cast<uint32_t*>(blk))[o] = full >> io.dbits;
+        G(reinterpret_cast<int16_t*>(blk + 12 * B))[o] = (int16_t)(full & dmask);
       } else {
         if (in) st_u32_nt(io.out_keys + dest[k], kk);
         else G(io.out_keys)[dest[k]] = kk;
@@ -1514,7 +1515,7 @@ __global__ __launch_bounds__(kCopyThreads) void k_copass_copy(BlockView v, CopyL
         const uint32_t tgt = G(reinterpret_cast<const uint32_t*>(blk + 4 * B))[q];
         const uint32_t w = G(reinterpret_cast<const uint32_t*>(blk + 8 * B))[q];
         const uint32_t d = (uint32_t)(uint16_t)G(reinterpret_cast<const int16_t*>(blk + 12 * B))[q];
-        G(keys)[cs.dst + o] = (src << v.dbits) | d;
+        G(keys)[cs.dst + o] = ((src << v.dbits) | d) - l.key_base;
         st_u32x2(pay + cs.dst + o, tgt, w);
       } else {
         const uint32_t kk = G(keys)[cs.src + o];
@@ -1753,6 +1754,7 @@ __global__ __launch_bounds__(kPartThreads) void k_copass_partition_samples(Copas
     p.status[0] = 1;
     p.status[1] = steps;
     p.status[2] = err;
+    p.status[3] = vlo;
   }
 }
 
@@ -1897,6 +1899,7 @@ __global__ __launch_bounds__(kPartThreads) void k_copass_partition(CopassPart p)
     p.status[0] = path;
     p.status[1] = iter;
     p.status[2] = err;
+    p.status[3] = ~0u;
   }
 }
 
