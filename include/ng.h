@@ -374,7 +374,7 @@ int ng_spikes_step(ng_ctx* ctx, const uint32_t* nodes, const uint32_t* mult, uin
  * are the same with either (stable order by (source, delay), Sec. 2.2).
  *   NG_CALIB_RADIX (default): stable radix sort of all connections into a
  *     second block set, in the most-significant-digit form (below) when one
- *     context with at least 2^23 connections is calibrated, its keys
+ *     context with at least 2^24 connections is calibrated, its keys
  *     (source bits + delay bits) fit in 27 bits, its connections average at
  *     least 256 per sub-bucket and at least 2.5 per possible key (n_nodes x
  *     2^delay bits), else in the LSD form.

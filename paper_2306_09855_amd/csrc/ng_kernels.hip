@@ -109,10 +109,11 @@ __global__ __launch_bounds__(kGenThreads) void k_generate_batch(const GenDesc* _
 //              stores that fill whole 128-byte lines are marked streaming.
 // Tiles are large (10,240 records, 512 threads) because the cost of a pass
 // is set by the length of the runs each tile writes per digit.  A pass over
-// few records takes tiles of 2,048 instead, as large tiles leave most of the
-// chip idle and a tile's serial phases set the time (sort_small_tiles;
-// downsweeps of a calibration, tiles of 10,240 and 2,048: 40 and 16 us at
-// 3e5 records, 104 and 73 at 4e6, 200 and 181 at 8e6).  Ranges are
+// fewer than 2^27 records takes tiles of 2,048 instead, three workgroups per
+// CU and one tile each: large tiles leave the chip idle in their serial
+// phases, and most of it where there are few (sort_small_tiles; downsweeps of
+// a calibration, tiles of 10,240 and 2,048: 40 and 16 us at 3e5 records, 104
+// and 60 at 4e6, 200 and 137 at 8e6, 2.52 and 1.97 ms at 1.2e8).  Ranges are
 // XCD-aware: workgroup w runs on XCD w % 8, and each XCD owns a contiguous
 // span of ranges, so the runs written by neighbouring ranges meet in one L2.
 // ---------------------------------------------------------------------------

@@ -576,7 +576,8 @@ struct CalSeg {
 void cal_ranges(CalSeg& g, bool small) {
   const uint64_t tile = ng::sort_tile_size(small), gi_tile = ng::gi_tile_size(small);
   const uint64_t n_tiles = (g.N + tile - 1) / tile;
-  g.tiles_per_range = (uint32_t)std::max<uint64_t>(1, (n_tiles + g.c->sort_ranges - 1) / g.c->sort_ranges);
+  const uint64_t most = ng::sort_max_ranges(g.c->sort_ranges, small);
+  g.tiles_per_range = (uint32_t)std::max<uint64_t>(1, (n_tiles + most - 1) / most);
   g.n_ranges = (uint32_t)((n_tiles + g.tiles_per_range - 1) / g.tiles_per_range);
   g.gi_tiles = (g.N + gi_tile - 1) / gi_tile;
 }
@@ -699,13 +700,13 @@ int calibrate_copass(ng_ctx* c) {
   const uint32_t k = (uint32_t)((N + B - 1) / B);
   const uint64_t A = std::max<uint64_t>(1, std::min<uint64_t>(B, N));  // the largest block
   const int P = g.passes, sbits = bitwidth(g.nn > 0 ? g.nn - 1 : 0);
-  // a sort of n <= A records uses ceil(tiles / ceil(tiles / sort_ranges)) <= min(sort_ranges, tiles) ranges
-  // of tiles of either size
+  // a sort of n <= A records uses ceil(tiles / ceil(tiles / most)) <= min(most, tiles) ranges of tiles of
+  // either size, most = the schedule's range count where the counts have their own array
   const bool gi_small = ng::sort_small_tiles(N);
   auto tiles_of = [](uint64_t n, bool small) { return (n + ng::sort_tile_size(small) - 1) / ng::sort_tile_size(small); };
+  const uint64_t max_ranges = std::max<uint64_t>(1, std::min<uint64_t>(c->sort_ranges, tiles_of(A, false)));
   uint64_t blk_tiles = tiles_of(A, ng::sort_small_tiles(A));
   if (!ng::sort_small_tiles(A) && k > 1 && ng::sort_small_tiles(N % B)) blk_tiles = std::max(blk_tiles, tiles_of(N % B, true));
-  const uint64_t max_ranges = std::max<uint64_t>(1, std::min<uint64_t>(c->sort_ranges, blk_tiles));
   uint32_t maxbits = 0;
   for (int p = 0; p < P; ++p) maxbits = std::max(maxbits, g.nbits[p]);
   const uint64_t counts_n = ((uint64_t)1 << maxbits) * max_ranges;
@@ -728,14 +729,19 @@ int calibrate_copass(ng_ctx* c) {
   uint32_t* scan_tmp = (uint32_t*)as.get(4 * tmp_words);
   uint32_t* part = (uint32_t*)as.get(4 * (7ull * std::max<uint32_t>(k, 1) + 4));
   ng::CopySeg* d_lists = (ng::CopySeg*)as.get(sizeof(ng::CopySeg) * seg_cap);
-  uint32_t* tile_flags = (uint32_t*)as.get(4 * (g.gi_tiles + 1));
+  // (the counts are idle by the time the group index is built)
+  uint32_t* tile_flags = g.gi_tiles + 1 <= counts_n ? counts : (uint32_t*)as.get(4 * (g.gi_tiles + 1));
   g.group_src = (uint32_t*)as.get(4 * g.gcap);
   g.bitmap = (uint32_t*)as.get(4 * ((N + 31) / 32 + 1));
   // The keys of one extracted block span a fraction of all keys, so that its
   // sort may need one pass less -- of wider digits than `counts` was sized
-  // for.  Their counts take the group index's arrays, idle until the blocks
-  // are sorted, when these have the room.
-  const uint64_t wide_n = ((uint64_t)1 << c->radix_bits) * max_ranges;
+  // for -- and small tiles sort best in more ranges than that.  Then the
+  // counts take the group index's arrays, idle until the blocks are sorted,
+  // when these have the room.
+  const uint64_t wide_ranges =
+      std::max<uint64_t>(max_ranges, std::min<uint64_t>(std::min(ng::sort_max_ranges(c->sort_ranges, true), blk_tiles),
+                                                        g.gcap >> c->radix_bits));
+  const uint64_t wide_n = ((uint64_t)1 << c->radix_bits) * wide_ranges;
   const bool wide = g.gcap >= wide_n && (N + 31) / 32 + 1 >= ng::scan_tmp_words(wide_n);
   uint32_t* wide_counts = wide ? g.group_src : nullptr;
   uint32_t* wide_tmp = wide ? g.bitmap : nullptr;
@@ -789,7 +795,8 @@ int calibrate_copass(ng_ctx* c) {
       const int P = dg.passes;
       const bool small = ng::sort_small_tiles(n);
       const uint64_t tiles = tiles_of(n, small);
-      const uint32_t tpr = (uint32_t)std::max<uint64_t>(1, (tiles + c->sort_ranges - 1) / c->sort_ranges);
+      const uint64_t most = wide_counts ? wide_ranges : max_ranges;
+      const uint32_t tpr = (uint32_t)std::max<uint64_t>(1, (tiles + most - 1) / most);
       const uint32_t nr = (uint32_t)((tiles + tpr - 1) / tpr);
       for (int p = 0; p < P; ++p) {
         ng::SortSeg sg{};
@@ -824,7 +831,7 @@ int calibrate_copass(ng_ctx* c) {
         pk.max_nbits = sg.nbits;
         pk.small_tiles = small;
         pk.self_offsets = nr <= ng::kSelfRanges;
-        const bool own = sg.nbits <= maxbits;
+        const bool own = !wide_counts;
         uint32_t *cnt = own ? counts : wide_counts, *tmp = own ? scan_tmp : wide_tmp;
         NG_LAUNCH(c, "upsweep", ng::launch_upsweep(pk, cnt, s));
         if (!pk.self_offsets)
@@ -1107,17 +1114,18 @@ bool msd_geometry(uint64_t N, uint32_t nn, int dbits, int log2B, uint32_t sort_r
 }
 
 // The default radix calibration takes the most-significant-digit form when
-// (1) there are at least 2^23 connections: below, the LSD passes need fewer
-// launches (calibration at 24 connections per possible key, LSD against MSD:
-// 0.20 and 0.20 ms at 4e6, 0.31 and 0.30 at 8e6, 0.42 and 0.36 at 1.2e7, 1.60
-// and 1.22 at 6e7); (2) the sub-buckets it must visit hold 256 connections on
+// (1) there are at least 2^24 connections: below, the LSD passes in small
+// tiles are faster (kernels of a build at 24 to 42 connections per possible
+// key, LSD against MSD: 0.30 and 0.34 ms at 9e6, 0.42 and 0.45 at 1.4e7, 0.58
+// and 0.59 at 2e7, 0.90 and 0.90 at 3.3e7, 1.21 and 1.13 at 4.5e7; whole
+// builds at 3e7 0.94 and 0.91); (2) the sub-buckets it must visit hold 256 connections on
 // average or more; and (3) there are at least 2.5 connections per possible
 // key (below, pass C sorts nearly empty tiles of 512 keys: 1.74 and 1.73 ms
 // at 2.8 per key and 5.4e7 uneven connections, 0.95 and 1.13 at 2.3 and
 // 2.9e7, 2.0 and 2.6 at 0.8 and 5.3e7; 14.4 and 11.0 at 6.9 and 4.4e8).
 bool msd_pays(const ng::MsdPlan& p) {
   const uint64_t keyspace = (uint64_t)p.n_nodes << p.dbits;
-  return p.n >= (1u << 23) && (uint64_t)p.n >= (256ull << (p.b1 + p.b2)) && (uint64_t)p.n * 2 >= keyspace * 5;
+  return p.n >= (1u << 24) && (uint64_t)p.n >= (256ull << (p.b1 + p.b2)) && (uint64_t)p.n * 2 >= keyspace * 5;
 }
 
 // The plan query's "2": large and dense enough that the form pays by a wide

@@ -46,13 +46,20 @@ def test_small_tiles(n, nodes):
     check_calibrated(out, gp, gs, ref, wl.calls)
 
 
-@pytest.mark.parametrize("n", [(1 << 23) - 1, 1 << 23])
-def test_both_tile_sizes_equal_the_msd_form(n):
+def _on_device(wl, calibration, block):
+    with _net(wl, block) as net:
+        net.set_calibration(calibration)
+        net.build(wl)
+        return (net.fetch(device=True), *net.group_index())
+
+
+@pytest.mark.parametrize("n,block", [((1 << 23) + 1, 1 << 20), ((1 << 27) - 1, 1 << 24), (1 << 27, 1 << 24)])
+def test_both_tile_sizes_equal_the_msd_form(n, block):
     wl = _wl(n, 30_000)
-    a, b = _sorted(wl, "lsd", 1 << 20), _sorted(wl, "msd", 1 << 20)
+    a, b = _on_device(wl, "lsd", block), _on_device(wl, "msd", block)
     for k in ("src", "tgt", "delay"):
-        assert np.array_equal(a[0][k], b[0][k]), k
-    assert np.array_equal(a[0]["w"].view(np.uint32), b[0]["w"].view(np.uint32))
+        assert torch.equal(a[0][k], b[0][k]), k
+    assert torch.equal(a[0]["w"].view(torch.int32), b[0]["w"].view(torch.int32))
     assert np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
 
 

@@ -71,12 +71,12 @@ def test_uneven_sources_equal_the_lsd_form(n_calls, n_nodes, hi_exp):
 
 
 def test_default_form_at_its_lower_bounds():
-    # from 2^23 connections and 2.5 per possible key on the default is the
+    # from 2^24 connections and 2.5 per possible key on the default is the
     # most-significant-digit form, below either bound the LSD form
     w, d = ("normal", 0.5, 0.05), ("uniform_int", 1, 31)
     n_dense = 20_000
-    at = [((1 << 23) - 1, n_dense, False), (1 << 23, n_dense, True),
-          (10_485_760, 1 << 17, True), (10_485_759, 1 << 17, False)]  # 2^17 nodes x 2^5 delays x 2.5
+    at = [((1 << 24) - 1, n_dense, False), (1 << 24, n_dense, True),
+          (20_971_520, 1 << 18, True), (20_971_519, 1 << 18, False)]  # 2^18 nodes x 2^5 delays x 2.5
     for n, nodes, msd in at:
         wl = W.Workload("bounds", 5, [nodes], [W.Call("fixed_total_number", (0, nodes), (0, nodes), n, w, d)])
         got = _arrays(wl, "radix", 1 << 22)
