@@ -308,8 +308,9 @@ int ng_copy_group_index(ng_ctx* ctx, uint32_t* group_ptr, uint32_t* group_start)
  * the key bits are split into the fewest passes of at most that width, as
  * evenly as possible (22-bit keys: 8+7+7; 26-bit keys: 9+9+8) -- and
  * the number of static ranges (one workgroup each) a sort pass splits the
- * connections into (1..2^20; default 1024).  Results do not depend on either;
- * speed does. */
+ * connections into (1..2^20; default 1024; the LSD form's passes over fewer
+ * than 2^27 connections take up to 64 times as many, of one small tile each).
+ * Results do not depend on either; speed does. */
 int ng_set_tuning(ng_ctx* ctx, int radix_bits, uint32_t sort_ranges);
 
 /* The whole kernel schedule of a context, for an autotuner (results never
