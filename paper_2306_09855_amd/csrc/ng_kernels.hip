@@ -595,7 +595,7 @@ __global__ __launch_bounds__(kSortThreads) void k_downsweep(SortPack pk, const u
 // ---------------------------------------------------------------------------
 // Device-wide exclusive scan (reduce, scan of partials, downsweep)
 // ---------------------------------------------------------------------------
-// A scan is short (2^18 counts for a block of 2^22 records) and its chain of
+// A scan is short (2^19 counts for a block of 2^22 records) and its chain of
 // loads sets its time: one 16-byte load per thread, 1,024 threads a tile
 // (2^18 counts, both launches: 7.8 us; 16 single words per thread in 256
 // threads 12.0 us).
