@@ -286,20 +286,22 @@ def ng_connect(ctx, src: ng_range, tgt: ng_range, conn: ng_conn_spec, syn: ng_sy
     return int(cid.value), int(first.value), int(n.value)
 
 
-def _structs(kind, items):
-    """C array of structures: the bytes of structures of this kind joined (a
-    quarter of the time of the array's constructor, which takes them one by
-    one and anything else the C structure can be made from)."""
-    if set(map(type, items)) != {kind}:
-        return (kind * len(items))(*items)
-    return (kind * len(items)).from_buffer_copy(b"".join(items))
+def _structs(kind, items, n):
+    """C array of n structures: the bytes of structures of this kind joined (a
+    quarter of the time of the array's constructor).  Anything else goes
+    through the constructor, which takes what the C structure can be made
+    from, leaves entries past a shorter list zero and refuses a longer one
+    with IndexError."""
+    if type(items) not in (list, tuple) or len(items) != n or set(map(type, items)) != {kind}:
+        return (kind * n)(*items)
+    return (kind * n).from_buffer_copy(b"".join(items))
 
 
 def ng_connect_batch(ctx, srcs, tgts, conns, syns):
     n = len(srcs)
     first = (ctypes.c_uint64 * n)()
-    _check(lib().ng_connect_batch(ctx, n, _structs(ng_range, srcs), _structs(ng_range, tgts),
-                                  _structs(ng_conn_spec, conns), _structs(ng_syn_spec, syns), first))
+    _check(lib().ng_connect_batch(ctx, n, _structs(ng_range, srcs, n), _structs(ng_range, tgts, n),
+                                  _structs(ng_conn_spec, conns, n), _structs(ng_syn_spec, syns, n), first))
     return list(first)
 
 
