@@ -212,12 +212,12 @@ struct MsdPlan {
   uint32_t* big_count;              // [2] sub-buckets larger than one LDS load, their pieces (set by pass C)
   uint2* big_list;                  // [max_big] (sub-bucket, its first piece)
   uint32_t* big_piece;              // [max_pieces] the list entry of each piece of kMsdBigPiece records
-  uint32_t* cnt_big;                // [max_pieces << b3] D3 counts of the pieces, then their first positions
   uint32_t max_pieces;              // n / kMsdBigPiece + max_big
-  uint32_t max_big;                 // n / (one load + 1) + 1
+  uint32_t max_big;                 // n / (one load + 1), at most the sub-buckets; 0: no such list
   uint32_t* gcount;                 // [2^(b1+b2) + 1] groups per sub-bucket, scanned in place
   uint32_t* gmask;                  // [2^(b1+b2) * mask_words] present D3 values per sub-bucket
-  uint32_t* gslot;                  // [n] local group starts at sub-bucket offsets (scratch)
+  uint32_t* gslot;                  // [n] local group starts at sub-bucket offsets, and behind those of a
+                                    // sub-bucket larger than one load its pieces' D3 counts (scratch)
   uint32_t mask_words;              // max(1, 2^b3 / 32)
   uint32_t* group_ptr;              // [n_nodes + 1]
   uint32_t* group_start;            // [min(n, 2^keybits) + 1]

@@ -1052,15 +1052,25 @@ __global__ __launch_bounds__(CSize<NARROW>::THREADS, CSize<NARROW>::WAVES_PER_SI
 // ms of the 4,096-call batch, whose calls draw from as little as one source
 // -- 1.7e8 of its 4.4e8 records are in such sub-buckets; in pieces 2.0 ms.
 // Pieces of 65,536 records: 0.22 ms instead of 0.14 at 3.3e7 connections.)
+// A sub-bucket's groups take at most 2^b3 words of gslot from its first record
+// on and leave the rest of its span free: piece j's counts lie 2^b3 words
+// after those of the piece before, the first behind the groups.
+static_assert((1ull + (CSize<true>::TILE + kMsdBigPiece) / kMsdBigPiece) * kMNB <= CSize<true>::TILE &&
+                  CSize<true>::TILE <= CSize<false>::TILE && kMNB <= (int)kMsdBigPiece,
+              "groups and piece counts fit in the span of a sub-bucket larger than one load");
+__device__ __forceinline__ uint32_t big_counts(uint32_t r0, uint32_t b3, uint32_t j) { return r0 + ((1u + j) << b3); }
+
 struct BigPiece {
   uint32_t sb, lo, hi;  // records [lo, hi) of sub-bucket sb
+  uint32_t counts;      // its D3 counts in gslot
 };
 __device__ __forceinline__ BigPiece big_piece(const MsdPlan& p, uint32_t i) {
   const u32x2 e = *(const NG_GLOBAL u32x2*)(p.big_list + G(p.big_piece)[i]);  // (sub-bucket, first piece)
   BigPiece q;
   q.sb = e.x;
-  const uint32_t end = G(p.sbstart)[q.sb + 1];
-  q.lo = G(p.sbstart)[q.sb] + (i - e.y) * kMsdBigPiece;
+  const uint32_t r0 = G(p.sbstart)[q.sb], end = G(p.sbstart)[q.sb + 1];
+  q.lo = r0 + (i - e.y) * kMsdBigPiece;
+  q.counts = big_counts(r0, p.b3, i - e.y);
   q.hi = end - q.lo < kMsdBigPiece ? end : q.lo + kMsdBigPiece;
   return q;
 }
@@ -1085,7 +1095,7 @@ __global__ __launch_bounds__(kCntThreads) void k_msd_big_count(MsdPlan p) {
       hist_add4(hist, (x.x >> f.ks) & m, (x.y >> f.ks) & m, (x.z >> f.ks) & m, (x.w >> f.ks) & m);
     }
     __syncthreads();
-    for (uint32_t d = threadIdx.x; d < nd; d += kCntThreads) p.cnt_big[((uint64_t)i << p.b3) + d] = hist[d];
+    for (uint32_t d = threadIdx.x; d < nd; d += kCntThreads) G(p.gslot)[q.counts + d] = hist[d];
   }
 }
 
@@ -1096,7 +1106,7 @@ __global__ __launch_bounds__(kMThreads) void k_msd_big_scan(MsdPlan p) {
     const u32x2 e = *(const NG_GLOBAL u32x2*)(p.big_list + i);
     const uint32_t r0 = G(p.sbstart)[e.x], n = G(p.sbstart)[e.x + 1] - r0;
     const uint32_t np = (n + kMsdBigPiece - 1) / kMsdBigPiece;
-    NG_GLOBAL uint32_t* cnt = G(p.cnt_big) + ((uint64_t)e.y << p.b3) + d;  // thread d: its D3 value's counts
+    NG_GLOBAL uint32_t* cnt = G(p.gslot) + big_counts(r0, p.b3, 0) + d;  // thread d: its D3 value's counts
     uint32_t h = 0;
     if (d < nd) {
 #pragma unroll 8
@@ -1136,7 +1146,7 @@ __global__ __launch_bounds__(CSize<NARROW>::THREADS, CSize<NARROW>::WAVES_PER_SI
   for (uint32_t i = blockIdx.x; i < n_pieces; i += gridDim.x) {
     const BigPiece q = big_piece(p, i);
     const uint32_t base = (q.sb << b3) & f.km;
-    if (d < nd) s_cur[d] = G(p.cnt_big)[((uint64_t)i << b3) + d];
+    if (d < nd) s_cur[d] = G(p.gslot)[q.counts + d];
     auto tile_cnt = [&](uint32_t c0) { return q.hi - c0 < CSize<NARROW>::TILE ? q.hi - c0 : CSize<NARROW>::TILE; };
     Recs<CSize<NARROW>::ITEMS> r;
     load_c<NARROW>(f.ik, f.it, f.iw, q.lo, tile_cnt(q.lo), r);
@@ -1286,9 +1296,11 @@ hipError_t launch_msd_tiles_c(const MsdPlan& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The grids are upper bounds: with nothing listed, three empty launches.
+// The grids are upper bounds: with nothing listed, three empty launches (none
+// when all connections fit one load).
 hipError_t launch_msd_big_c(const MsdPlan& p, hipStream_t s) {
   const bool narrow = p.b2 ? p.narrow_b : p.narrow_a;
+  if (p.max_big == 0) return hipSuccess;
   const dim3 pieces(std::min(p.max_pieces, 1024u));
   if (narrow) hipLaunchKernelGGL(k_msd_big_count<true>, pieces, dim3(kCntThreads), 0, s, p);
   else hipLaunchKernelGGL(k_msd_big_count<false>, pieces, dim3(kCntThreads), 0, s, p);

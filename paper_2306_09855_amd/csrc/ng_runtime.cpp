@@ -1105,8 +1105,8 @@ bool msd_geometry(uint64_t N, uint32_t nn, int dbits, int log2B, uint32_t sort_r
   const uint64_t work = N + (uint64_t)p.nsb_used * p.sb_cost;
   const uint64_t rounds = std::max<uint64_t>((work / (4 * piece) + 256) / 512, 2);
   p.wgs_c = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, std::min<uint64_t>(512 * rounds, nsb)), 1u << 20);
-  p.max_big = (uint32_t)(N / (piece + 1) + 1);
-  p.max_pieces = (uint32_t)(N / ng::kMsdBigPiece + p.max_big);
+  p.max_big = (uint32_t)std::min<uint64_t>(N / (piece + 1), nsb);
+  p.max_pieces = p.max_big ? (uint32_t)(N / ng::kMsdBigPiece + p.max_big) : 0u;
   p.n_nodes = nn;
   p.log2B = log2B;
   p.mask_words = std::max<uint32_t>(1, (1u << b3) / 32);
@@ -1172,11 +1172,17 @@ int calibrate_msd(CalSeg& g, const ng::MsdPlan& plan) {
   p.sbstart = (uint32_t*)as.get(4 * (nsb + 1));
   p.gcount = (uint32_t*)as.get(4 * (nsb + 1));
   p.gmask = (uint32_t*)as.get(4 * nsb * p.mask_words);
-  p.wg_sb0 = (uint32_t*)as.get(4 * ((uint64_t)p.wgs_c + 1));
+  // Pass C's own tables take what is dead by then and asks for no more of the
+  // arena: the split, B's counts (at least 3 words more than there are
+  // sub-buckets); the lists, A's weights or counts.
+  p.wg_sb0 = p.b2 ? p.cnt_b : (uint32_t*)as.get(4 * ((uint64_t)p.wgs_c + 1));
   p.big_count = (uint32_t*)as.get(8);
-  p.big_list = (uint2*)as.get(8 * (uint64_t)p.max_big);
-  p.big_piece = (uint32_t*)as.get(4 * (uint64_t)p.max_pieces);
-  p.cnt_big = (uint32_t*)as.get((4ull * p.max_pieces) << p.b3);
+  if (p.max_big) {
+    const uint64_t words = 2 * (uint64_t)p.max_big + p.max_pieces, room = p.b2 ? N : na;
+    uint32_t* lists = words > room ? (uint32_t*)as.get(4 * words) : (p.b2 ? p.a_w : p.cnt_a);
+    p.big_list = (uint2*)lists;
+    p.big_piece = lists ? lists + 2 * (uint64_t)p.max_big : nullptr;
+  }
   g.gp_bytes = 4 * (g.nn + 1ull);
   g.gs_bytes = 4 * g.gcap;
   release_index(c);

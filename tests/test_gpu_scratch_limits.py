@@ -1,0 +1,93 @@
+"""What a calibration asks of its arena, and what it does when the arena does
+not have it: results in arenas of just the size, bit for bit against an
+ordinary build in the LSD form."""
+import numpy as np
+import pytest
+
+from paper_2306_09855_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2306_09855_amd import ng  # noqa: E402
+from paper_2306_09855_amd.network import Network, arena_bytes_for  # noqa: E402
+
+
+def _up(nbytes):
+    return max(256, -(-nbytes // 256) * 256)  # arena allocations come in 256 bytes
+
+
+def _wl(n, nodes, delay):
+    """n connections, a third of them from one source."""
+    w, d = ("normal", 0.5, 0.05), ("uniform_int", 1, delay)
+    return W.Workload("limits", 7, [nodes],
+                      [W.Call("fixed_total_number", (nodes // 2, 1), (0, nodes), n // 3, w, d),
+                       W.Call("fixed_total_number", (0, nodes), (0, nodes), n - n // 3, w, d)])
+
+
+class _Built:
+    """The workload's connections in an arena of `arena` bytes (None: ample),
+    calibrated in `form`: arrays, index, kernels launched and arena bytes."""
+
+    def __init__(self, wl, form, block, arena=None, calibrate=ng.ng_calibrate):
+        ample = arena_bytes_for(wl.n_syn, wl.n_nodes, wl.max_delay, block) + 24 * wl.n_syn
+        with Network(wl.seed, wl.h, block, arena or ample) as net:
+            net.set_calibration(form)
+            net.build(wl, calibrate=False)
+            net.sync()
+            self.before = net.memory_stats()[0]
+            ng.ng_enable_timing(net.ctx, True)
+            calibrate(net.ctx)
+            self.kernels = set(ng.ng_read_timing(net.ctx, reset=True))
+            _, self.peak, _ = net.memory_stats()
+            self.arrays = net.fetch(device=True)
+            self.index = net.group_index()
+
+    def same(self, other):
+        for k in ("src", "tgt", "delay"):
+            assert torch.equal(self.arrays[k], other.arrays[k]), k
+        assert torch.equal(self.arrays["w"].view(torch.int32), other.arrays["w"].view(torch.int32))
+        assert np.array_equal(self.index[0], other.index[0]) and np.array_equal(self.index[1], other.index[1])
+
+
+def _msd_bytes(n, nodes, delay, block, ranges=1024):
+    """The calibrated blocks, index and scratch of the most-significant-digit
+    form: the records of each pass, a group slot per connection, the digit
+    counts and tables, and a word per 10,241 connections for lists."""
+    p = ng.ng_calibration_plan(n, nodes, delay, ranges)
+    assert p["msd"] >= 1
+    rec_a, rec_b = (8 if p["narrow_a"] else 12), (8 if p["narrow_b"] else 12)
+    nb, nsb = 1 << p["b1"], 1 << (p["b1"] + p["b2"])
+    na = nb * -(-(-(-n // 10240)) // p["tpr"])
+    nbc = (3 * ranges + nb) << p["b2"] if p["b2"] else 0
+    scan = max(-(-x // 4096) + 1 for x in (na, nbc, nsb))
+    split = min(max(-(-n // 61440), 1024), nsb)
+    sizes = [4 * n] * (rec_a // 4 + (rec_b // 4 if p["b2"] else 1)) + [4 * na]
+    sizes += [4 * nbc] if p["b2"] else []
+    sizes += [4 * scan, 4 * (nb + 1), 4 * (nb + 1), 4 * nb, 4 * (nsb + 1), 4 * (nsb + 1),
+              4 * nsb * max(1, (1 << p["b3"]) // 32), 4 * (split + 1), 4, 4 * (n // 10241 + 1),
+              4 * (nodes + 1), 4 * (min(n, nodes * delay) + 1)]
+    return sum(map(_up, sizes)) + -(-n // block) * 14 * block
+
+
+@pytest.mark.parametrize("n,nodes,delay", [
+    (5_000, 2_000, 7),           # less than one LDS load
+    (2_000_001, 30_000, 31),     # two scatters, packed records, 9-bit last digit
+    (3_000_000, 100, 3),         # one scatter
+    (2_500_000, 1 << 24, 3),     # unpacked records
+])
+def test_msd_form_in_its_bytes(n, nodes, delay):
+    block = 1 << 18
+    wl = _wl(n, nodes, delay)
+    need = _msd_bytes(n, nodes, delay, block)
+    ample = _Built(wl, "msd", block)
+    assert "msd_tiles_c" in ample.kernels
+    assert ample.peak - ample.before <= need
+    tight = _Built(wl, "msd", block, ample.before + need)
+    lsd = _Built(wl, "lsd", block)
+    assert "downsweep" in lsd.kernels
+    ample.same(lsd)
+    tight.same(lsd)
