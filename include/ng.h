@@ -380,7 +380,8 @@ int ng_spikes_step(ng_ctx* ctx, const uint32_t* nodes, const uint32_t* mult, uin
  *     least 256 per sub-bucket and at least 2.5 per possible key (n_nodes x
  *     2^delay bits), else in the LSD form.
  *   NG_CALIB_RADIX_MSD: the most-significant-digit form whenever one context
- *     with keys of at most 27 bits is calibrated (else LSD): a scatter by
+ *     with keys of at most 27 bits and at most 2^32 - 2^15 connections is
+ *     calibrated (else LSD): a scatter by
  *     the top digit, a scatter of each bucket by the second digit, and runs
  *     of whole sub-buckets sorted by the last digit in on-chip memory and
  *     written straight into the calibrated blocks with their connection
@@ -546,8 +547,8 @@ uint64_t ng_blocks_needed(uint64_t n_conns, uint64_t n_new, uint64_t block_size,
  * margin (at least 2^25, 256 per sub-bucket and 10 per possible key; the
  * default calibration takes it then, and from the lower bounds given at
  * NG_CALIB_RADIX on), 1 when the form applies otherwise, 0 when it does not
- * apply (keys wider than 27 bits, n_conns = 0 or >= 2^32; the rest is then
- * zero); out[1..3] = the widths b1, b2, b3 of the digits from the top (b2 = 0: no second scatter); out[4], out[5] =
+ * apply (keys wider than 27 bits, n_conns = 0 or > 2^32 - 2^15; the rest is
+ * then zero); out[1..3] = the widths b1, b2, b3 of the digits from the top (b2 = 0: no second scatter); out[4], out[5] =
  * 1 when the records after the first / second scatter pack the remaining
  * key bits and the target into one word; out[6] = workgroups of the
  * in-LDS pass; out[7] = tiles per range.  Returns NG_OK, or

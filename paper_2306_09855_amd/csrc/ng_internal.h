@@ -180,6 +180,11 @@ constexpr uint32_t kMsdTileN = 16384;     // records per tile of B with packed (
 constexpr uint32_t kMsdBigPiece = 16384;   // records per piece of a sub-bucket larger than one LDS load
 constexpr uint32_t kMsdMaxDigit = 9;      // widest digit
 constexpr uint32_t kMsdMaxKeyBits = 27;   // 3 x kMsdMaxDigit
+// The kernels hold positions in 32 bits and step past the last record by up to
+// a tile, a piece or a workgroup: with this many connections at most none of
+// these sums wraps.
+constexpr uint64_t kMsdMaxConns = (1ull << 32) - (1ull << 15);
+static_assert(kMsdTileN <= (1u << 15) && kMsdTile <= (1u << 15) && kMsdBigPiece <= (1u << 15), "steps past the end");
 
 struct MsdPlan {
   uint32_t n;                       // records (n > 0)

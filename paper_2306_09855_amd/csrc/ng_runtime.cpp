@@ -1041,7 +1041,7 @@ bool msd_geometry(uint64_t N, uint32_t nn, int dbits, int log2B, uint32_t sort_r
                   uint32_t msd_tile = 0) {
   const int sbits = bitwidth(nn > 0 ? nn - 1 : 0);
   const int K = sbits + dbits;
-  if (N == 0 || N > 0xFFFFFFFFull || K < 2 || K > (int)ng::kMsdMaxKeyBits) return false;
+  if (N == 0 || N > ng::kMsdMaxConns || K < 2 || K > (int)ng::kMsdMaxKeyBits) return false;
   const uint32_t tbits = (uint32_t)std::max(1, sbits);
   const uint64_t keyspace = (uint64_t)nn << dbits;
   const uint64_t cap = ng::msd_cap(tbits + ng::kMsdMaxDigit <= 32);
