@@ -378,7 +378,8 @@ int ng_spikes_step(ng_ctx* ctx, const uint32_t* nodes, const uint32_t* mult, uin
  *     context with at least 2^24 connections is calibrated, its keys
  *     (source bits + delay bits) fit in 27 bits, its connections average at
  *     least 256 per sub-bucket and at least 2.5 per possible key (n_nodes x
- *     2^delay bits), else in the LSD form.
+ *     2^delay bits), else -- and where the arena has no room for that form's
+ *     scratch -- in the LSD form.
  *   NG_CALIB_RADIX_MSD: the most-significant-digit form whenever one context
  *     with keys of at most 27 bits and at most 2^32 - 2^15 connections is
  *     calibrated (else LSD): a scatter by

@@ -1347,14 +1347,20 @@ int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, Scratc
     g.sb = sb;
   }
   // one context with its own scratch: the most-significant-digit sort when
-  // its keys fit
+  // its keys fit.  It needs 16 bytes of scratch per connection or more, the
+  // LSD form 12 where the keys take two passes: without arena room the default
+  // goes on in the LSD form (nothing was launched)
+  uint64_t msd_need = ~0ull;
   if (segs.size() == 1 && !sb &&
       (segs[0].c->calib_mode == NG_CALIB_RADIX || segs[0].c->calib_mode == NG_CALIB_RADIX_MSD)) {
     ng::MsdPlan mp;
     const CalSeg& g = segs[0];
     if (msd_geometry(g.N, g.nn, g.dbits, g.c->log2B, g.c->sort_ranges, mp, g.c->msd_tile) &&
-        (g.c->calib_mode == NG_CALIB_RADIX_MSD || msd_pays(mp)))
-      return calibrate_msd(segs[0], mp);
+        (g.c->calib_mode == NG_CALIB_RADIX_MSD || msd_pays(mp))) {
+      const int rc = calibrate_msd(segs[0], mp);
+      if (rc != NG_ERR_OOM || g.c->calib_mode == NG_CALIB_RADIX_MSD) return rc;
+      msd_need = g.c->need;
+    }
   }
   // few records in all: small tiles, or large ones where the arena (or the
   // fixed scratch) has no room for the larger count arrays of small ones
@@ -1369,7 +1375,9 @@ int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, Scratc
       sb->ok = true;
     }
   }
-  return calibrate_lsd(segs, upload, sb, false);
+  const int rc = calibrate_lsd(segs, upload, sb, false);
+  if (rc == NG_ERR_OOM) segs[0].c->need = std::min(segs[0].c->need, msd_need);  // room for either form would do
+  return rc;
 }
 
 namespace {

@@ -91,3 +91,65 @@ def test_msd_form_in_its_bytes(n, nodes, delay):
     assert "downsweep" in lsd.kernels
     ample.same(lsd)
     tight.same(lsd)
+
+
+def test_default_form_goes_on_without_room_for_msd():
+    # 17-bit keys: 16 bytes of scratch per connection for the MSD form, 12
+    # (two passes) for the LSD form
+    n, nodes, delay, block = (1 << 24) + 5, 4096, 31, 1 << 22
+    wl = _wl(n, nodes, delay)
+    ample = _Built(wl, "radix", block)
+    assert "msd_tiles_c" in ample.kernels and "downsweep" not in ample.kernels
+    blocks = -(-n // block) * 14 * block
+    between = _Built(wl, "radix", block, ample.before + blocks + 14 * n)
+    assert "downsweep" in between.kernels and "msd_tiles_c" not in between.kernels
+    between.same(ample)
+    with pytest.raises(ng.NGError) as e:  # the form asked for by name is not replaced
+        _Built(wl, "msd", block, ample.before + blocks + 14 * n)
+    assert e.value.status == ng.NG_ERR_OOM
+    with pytest.raises(ng.NGError) as e:  # no room for either
+        _Built(wl, "radix", block, ample.before + blocks + 11 * n)
+    assert e.value.status == ng.NG_ERR_OOM
+
+
+# The LSD form's small tiles bring more digit counts than its large ones, which
+# it goes back to where the arena or the fixed scratch has no room for them.
+def _lsd_bytes(n, nodes, delay, block, small, ranges=1024, radix_bits=9):
+    sbits, dbits = max(nodes - 1, 0).bit_length(), delay.bit_length()
+    passes = -(-(sbits + dbits) // radix_bits)
+    digit = -(-(sbits + dbits) // passes)
+    tile, most, gi_tile = (2048, 64 * ranges, 2048) if small else (10240, ranges, 8192)
+    tiles = -(-n // tile)
+    per = max(1, -(-tiles // most))
+    counts = (1 << digit) * -(-tiles // per)
+    gcap = min(n, nodes * delay) + 1
+    gi = -(-n // gi_tile)
+    sizes = [4 * n, 8 * n] * min(passes - 1, 2) + [4 * gcap, 4 * (-(-n // 32) + 1), 4 * counts,
+                                                   4 * (max(-(-counts // 4096), -(-gi // 4096)) + 1), 4 * (gi + 1)]
+    index = [4 * (nodes + 1), 4 * gcap]
+    return sum(map(_up, sizes)), sum(map(_up, index)) + -(-n // block) * 14 * block
+
+
+def test_lsd_large_tiles_where_small_ones_have_no_room():
+    n, nodes, delay, block = 2_000_003, 30_000, 31, 1 << 18
+    wl = _wl(n, nodes, delay)
+    ample = _Built(wl, "lsd", block)
+    small, large = (sum(_lsd_bytes(n, nodes, delay, block, s)) for s in (True, False))
+    assert ample.peak - ample.before == small and large < small
+    tight = _Built(wl, "lsd", block, ample.before + large)
+    assert tight.peak - tight.before <= large
+    tight.same(ample)
+    with pytest.raises(ng.NGError) as e:
+        _Built(wl, "lsd", block, ample.before + large - (1 << 16))
+    assert e.value.status == ng.NG_ERR_OOM
+
+
+def test_fixed_scratch_large_tiles_where_small_ones_have_no_room():
+    nodes, delay, block = 1 << 22, 31, 1 << 18  # 27-bit keys: three passes, 512 digit values
+    region = ng.ng_noalloc_scratch_bytes()
+    n = next(n for n in range(2_400_000, 2_000_000, -1000)
+             if _lsd_bytes(n, nodes, delay, block, False)[0] <= region)
+    assert _lsd_bytes(n, nodes, delay, block, True)[0] > region
+    wl = _wl(n, nodes, delay)
+    fixed = _Built(wl, "lsd", block, calibrate=ng.ng_calibrate_noalloc)
+    fixed.same(_Built(wl, "lsd", block))
