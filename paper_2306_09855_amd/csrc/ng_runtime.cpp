@@ -702,7 +702,6 @@ int calibrate_copass(ng_ctx* c) {
   const int P = g.passes, sbits = bitwidth(g.nn > 0 ? g.nn - 1 : 0);
   // a sort of n <= A records uses ceil(tiles / ceil(tiles / most)) <= min(most, tiles) ranges of tiles of
   // either size, most = the schedule's range count where the counts have their own array
-  const bool gi_small = ng::sort_small_tiles(N);
   auto tiles_of = [](uint64_t n, bool small) { return (n + ng::sort_tile_size(small) - 1) / ng::sort_tile_size(small); };
   const uint64_t max_ranges = std::max<uint64_t>(1, std::min<uint64_t>(c->sort_ranges, tiles_of(A, false)));
   uint64_t blk_tiles = tiles_of(A, ng::sort_small_tiles(A));
@@ -710,6 +709,11 @@ int calibrate_copass(ng_ctx* c) {
   uint32_t maxbits = 0;
   for (int p = 0; p < P; ++p) maxbits = std::max(maxbits, g.nbits[p]);
   const uint64_t counts_n = ((uint64_t)1 << maxbits) * max_ranges;
+  // small tiles of the group index where their flags fit in the counts, idle
+  // by then: blocks of 2^16 have too few counts for many such blocks' tiles
+  const uint64_t gi_tile = ng::gi_tile_size(true);
+  const bool gi_small = ng::sort_small_tiles(N) && (N + gi_tile - 1) / gi_tile < counts_n;
+  cal_ranges(g, gi_small);
   const uint64_t seg_cap = 5ull * k + 8;  // copy pieces of one step
   // the partition results are read back through pinned words: had before
   // anything moves, so that failing to get them changes nothing
@@ -729,7 +733,6 @@ int calibrate_copass(ng_ctx* c) {
   uint32_t* scan_tmp = (uint32_t*)as.get(4 * tmp_words);
   uint32_t* part = (uint32_t*)as.get(4 * (7ull * std::max<uint32_t>(k, 1) + 4));
   ng::CopySeg* d_lists = (ng::CopySeg*)as.get(sizeof(ng::CopySeg) * seg_cap);
-  // (the counts are idle by the time the group index is built)
   uint32_t* tile_flags = g.gi_tiles + 1 <= counts_n ? counts : (uint32_t*)as.get(4 * (g.gi_tiles + 1));
   g.group_src = (uint32_t*)as.get(4 * g.gcap);
   g.bitmap = (uint32_t*)as.get(4 * ((N + 31) / 32 + 1));

@@ -153,3 +153,35 @@ def test_fixed_scratch_large_tiles_where_small_ones_have_no_room():
     wl = _wl(n, nodes, delay)
     fixed = _Built(wl, "lsd", block, calibrate=ng.ng_calibrate_noalloc)
     fixed.same(_Built(wl, "lsd", block))
+
+
+def _copass_bytes(n, nodes, delay, block, radix_bits=9, ranges=1024):
+    """Scratch and index of the in-place block sort: an auxiliary block and one
+    or two sort buffers, the digit counts of one block's large tiles, the
+    partition's words and copy lists, and the group index's arrays."""
+    sbits, dbits = max(nodes - 1, 0).bit_length(), delay.bit_length()
+    passes = -(-(sbits + dbits) // radix_bits)
+    blocks, a = -(-n // block), min(n, block)
+    counts = (1 << -(-(sbits + dbits) // passes)) * min(ranges, -(-a // 10240))
+    gcap, gi = min(n, nodes * delay) + 1, -(-n // 8192)
+    sizes = [4 * a, 8 * a] * (3 if passes >= 3 else 2)
+    sizes += [4 * counts, 4 * (max(-(-counts // 4096), -(-gi // 4096)) + 1), 4 * (7 * blocks + 4), 16 * (5 * blocks + 8),
+              4 * (gi + 1), 4 * gcap, 4 * (-(-n // 32) + 1), 4 * (nodes + 1), 4 * gcap]
+    return sum(map(_up, sizes))
+
+
+@pytest.mark.parametrize("n,nodes,delay,block", [
+    (6_000_000, 50, 3, 1 << 16),             # 8-bit keys: more tiles of the group index than counts
+    (800_000, 9_000, 31, 1 << 16),
+    (3 * (1 << 20) + 77, 2_000, 20, 1 << 20),  # no room in the index's arrays for wider digits or more ranges
+])
+def test_copass_in_its_bytes(n, nodes, delay, block):
+    wl = _wl(n, nodes, delay)
+    need = _copass_bytes(n, nodes, delay, block)
+    ample = _Built(wl, "copass", block)
+    assert "copass_partition" in ample.kernels
+    assert ample.peak - ample.before <= need
+    tight = _Built(wl, "copass", block, ample.before + need)
+    lsd = _Built(wl, "lsd", block)
+    ample.same(lsd)
+    tight.same(lsd)
