@@ -10,6 +10,7 @@
 // the sort section), then the connection-group index (Eq. (14)).
 #include "ng_internal.h"
 #include "ng_device.h"
+#include "ng_search.h"
 
 namespace ng {
 namespace {
@@ -1631,17 +1632,6 @@ __device__ __forceinline__ void part_bounds(const uint32_t* s_key, uint32_t lo, 
   u = c < n ? part_pos(lo, hi, q, c) : hi;
 }
 
-// Keys x_t = a + floor((b - a)(t + 1) / 9), t < 8; f: the first t whose key is
-// at or past the sought one (8: none); b itself is.
-__device__ __forceinline__ uint32_t part_probe(uint32_t a, uint32_t b, uint32_t t) {
-  return a + (uint32_t)((uint64_t)(b - a) * (t + 1) / 9);
-}
-__device__ __forceinline__ void part_narrow(uint32_t& a, uint32_t& b, uint32_t f) {
-  const uint32_t na = f > 0 ? part_probe(a, b, f - 1) + 1 : a;
-  if (f < 8) b = part_probe(a, b, f);
-  a = na;
-}
-
 __global__ __launch_bounds__(kPartThreads) void k_copass_partition_samples(CopassPart p) {
   __shared__ uint32_t s_key[kPartKeys];
   __shared__ uint32_t s_start[kPartMaxSub], s_lo[kPartMaxSub], s_hi[kPartMaxSub], s_c[kPartMaxSub];
@@ -1681,7 +1671,8 @@ __global__ __launch_bounds__(kPartThreads) void k_copass_partition_samples(Copas
       if (j < min(hi - lo, S)) s_key[i * (S + 1) + j] = view_key(p.v, s_start[i] + part_pos(lo, hi, q, j));
     }
     __syncthreads();
-    // smallest key whose upper bounds (waves 0-7) and lower bounds (8-15) reach m
+    // smallest key whose upper bounds (waves 0-7) and lower bounds (8-15)
+    // reach m; the upper ones do at vhi, the lower ones perhaps nowhere
     uint32_t a0 = vlo, b0 = vhi, a1 = vlo, b1 = vhi, par = 0;
     while (a0 < b0 || a1 < b1) {
       const uint32_t x = wave < 8 ? part_probe(a0, b0, wave) : part_probe(a1, b1, wave - 8);
