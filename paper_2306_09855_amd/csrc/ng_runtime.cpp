@@ -1248,15 +1248,17 @@ int calibrate_lsd(std::vector<CalSeg>& segs, const Uploader* upload, ScratchBump
 
 // The queued Connect calls of the contexts on the first one's stream (one
 // block size) as one upload -- block-table entries and descriptors, each
-// naming its context's table and key -- and one generation launch.  Without
-// arena room for the upload nothing happens here: each context launches its
-// own queue.
+// naming its context's table and key -- and one generation launch.  A context
+// that times its generation launches its own queue, whose time and synapses
+// its ng_read_timing reports; without arena room for the upload every context
+// does.
 int flush_connects_packed(ng_ctx* const* cs, uint32_t n) {
   ng_ctx* c0 = cs[0];
   std::vector<ng_ctx*> with;
   uint64_t n_entries = 0, n_descs = 0;
   for (uint32_t i = 0; i < n; ++i)
-    if (!cs[i]->queued.empty() && cs[i]->stream == c0->stream && cs[i]->gen_quads == c0->gen_quads) {
+    if (!cs[i]->queued.empty() && cs[i]->stream == c0->stream && cs[i]->gen_quads == c0->gen_quads &&
+        !timed_launch(cs[i], "generate_batch")) {
       with.push_back(cs[i]);
       n_entries += cs[i]->blocks.size() - cs[i]->tab_synced;
       n_descs += cs[i]->queued.size();
