@@ -66,13 +66,19 @@ def moved_bytes(kernel: str, n_syn: int, plan: dict) -> float | None:
     """Bytes the implementation's kernel reads and writes per step (records
     of 14 bytes in blocks, 8 bytes packed, 12 bytes unpacked between
     passes); a diagnostic next to the algorithmic figure."""
-    if not plan or plan.get("msd", 0) != 2:
+    if not plan or not plan.get("msd", 0):
         return None
     a = 8.0 if plan["narrow_a"] else 12.0
     b = 8.0 if plan["narrow_b"] else 12.0
     per = {"msd_count_a": 4.0, "msd_scatter_a": 14.0 + a, "msd_count_b": 4.0,
            "msd_scatter_b": a + b, "msd_tiles_c": (b if plan["b2"] else a) + 14.0}.get(kernel)
     return None if per is None else per * n_syn
+
+
+def calibrated_msd(kernels) -> bool:
+    """Whether the calibration ran in the most-significant-digit form, from the
+    names of the kernels timed."""
+    return any(name.startswith("msd_") for name in kernels)
 
 
 def kernels_fingerprint(kernel: str) -> str:
@@ -834,8 +840,7 @@ def main() -> int:
     value = args.steps * n_syn / wall
 
     plan = ng.ng_calibration_plan(n_syn, wl.n_nodes, wl.max_delay, schedule["sort_ranges"])
-    cal = schedule["calibration"]
-    msd = plan["msd"] == 2 and cal == "radix" or (cal == "msd" and plan["msd"] >= 1)
+    msd = calibrated_msd(kernels)
     dbits = int(wl.max_delay).bit_length()
     sbits = int(wl.n_nodes - 1).bit_length()
     lsd_passes = max(1, -(-(sbits + dbits) // schedule["radix_bits"]))

@@ -540,22 +540,28 @@ const char* ng_last_error(void);
 uint64_t ng_blocks_needed(uint64_t n_conns, uint64_t n_new, uint64_t block_size,
                           uint64_t n_blocks);
 
-/* Digit plan that the default calibration (NG_CALIB_RADIX) takes for one
- * context of n_conns connections over n_nodes nodes whose delays are at most
- * max_delay steps, with sort_ranges static ranges per scatter pass (the
- * ng_set_tuning value, 1024 by default).  out[0] = 2 when the connections
- * are many and dense enough for the most-significant-digit form by a wide
- * margin (at least 2^25, 256 per sub-bucket and 10 per possible key; the
- * default calibration takes it then, and from the lower bounds given at
- * NG_CALIB_RADIX on), 1 when the form applies otherwise, 0 when it does not
- * apply (keys wider than 27 bits, n_conns = 0 or > 2^32 - 2^15; the rest is
- * then zero); out[1..3] = the widths b1, b2, b3 of the digits from the top (b2 = 0: no second scatter); out[4], out[5] =
- * 1 when the records after the first / second scatter pack the remaining
- * key bits and the target into one word; out[6] = workgroups of the
- * in-LDS pass; out[7] = tiles per range.  Returns NG_OK, or
- * NG_ERR_INVALID_ARG for a null out or max_delay < 1. */
+/* Digit plan of the most-significant-digit form for one context of n_conns
+ * connections over n_nodes nodes whose delays are at most max_delay steps,
+ * with sort_ranges static ranges per scatter pass (the ng_set_tuning value,
+ * 1024 by default).  out[0] = 0 when the form does not apply (keys wider than
+ * 27 bits, n_conns = 0 or > 2^32 - 2^15; the rest is then zero), 2 when it
+ * does and the connections are at least 2^25, 256 per sub-bucket and 10 per
+ * possible key, else 1 (ng_calibration_form says which form the default
+ * calibration takes); out[1..3] = the widths b1, b2, b3 of the digits from
+ * the top (b2 = 0: no second scatter); out[4], out[5] = 1 when the records
+ * after the first / second scatter pack the remaining key bits and the target
+ * into one word; out[6] = workgroups of the in-LDS pass; out[7] = tiles per
+ * range.  Returns NG_OK, or NG_ERR_INVALID_ARG for a null out or
+ * max_delay < 1. */
 int ng_calibration_plan(uint64_t n_conns, uint32_t n_nodes, int32_t max_delay, uint32_t sort_ranges,
                         uint32_t out[8]);
+
+/* The form that the default calibration (NG_CALIB_RADIX) of one such context
+ * takes: *form = NG_CALIB_RADIX_MSD from the bounds given there on, where its
+ * arena has the room, else NG_CALIB_RADIX_LSD.  Returns NG_OK, or
+ * NG_ERR_INVALID_ARG for a null form or max_delay < 1. */
+int ng_calibration_form(uint64_t n_conns, uint32_t n_nodes, int32_t max_delay, uint32_t sort_ranges,
+                        int32_t* form);
 
 /* Validate a Connect call against n_nodes existing nodes and return the
  * number of connections it creates (Sec. 2.1). */

@@ -1131,9 +1131,8 @@ bool msd_pays(const ng::MsdPlan& p) {
   return p.n >= (1u << 24) && (uint64_t)p.n >= (256ull << (p.b1 + p.b2)) && (uint64_t)p.n * 2 >= keyspace * 5;
 }
 
-// The plan query's "2": large and dense enough that the form pays by a wide
-// margin (at least 2^25 connections and 10 per possible key); msd_pays holds
-// for every such plan.
+// The plan query's "2": at least 2^25 connections and 10 per possible key;
+// msd_pays holds for every such plan.
 bool msd_dense(const ng::MsdPlan& p) {
   const uint64_t keyspace = (uint64_t)p.n_nodes << p.dbits;
   return msd_pays(p) && p.n >= (1u << 25) && (uint64_t)p.n * 512 >= keyspace * (ng::kMsdTile / 2);
@@ -1716,6 +1715,15 @@ int ng_calibration_plan(uint64_t n_conns, uint32_t n_nodes, int32_t max_delay, u
     return NG_OK;
   const uint32_t v[8] = {msd_dense(p) ? 2u : 1u, p.b1, p.b2, p.b3, p.narrow_a, p.narrow_b, p.wgs_c, p.tpr};
   for (int i = 0; i < 8; ++i) out[i] = v[i];
+  return NG_OK;
+}
+
+int ng_calibration_form(uint64_t n_conns, uint32_t n_nodes, int32_t max_delay, uint32_t sort_ranges, int32_t* form) {
+  if (!form || max_delay < 1) return fail(NG_ERR_INVALID_ARG, "null output or max_delay < 1");
+  ng::MsdPlan p;
+  const bool msd =
+      msd_geometry(n_conns, n_nodes, bitwidth((uint64_t)max_delay), 24, sort_ranges ? sort_ranges : 1024, p) && msd_pays(p);
+  *form = msd ? NG_CALIB_RADIX_MSD : NG_CALIB_RADIX_LSD;
   return NG_OK;
 }
 

@@ -170,6 +170,7 @@ def lib():
             "ng_plan_count": ([u32, ng_range, ng_range, P(ng_conn_spec), P(ng_syn_spec), ctypes.c_float,
                                P(u64)], ctypes.c_int),
             "ng_calibration_plan": ([u64, u32, i32, u32, P(u32)], ctypes.c_int),
+            "ng_calibration_form": ([u64, u32, i32, u32, P(i32)], ctypes.c_int),
             "ng_version": ([], ctypes.c_char_p),
         }
         for name, (args, res) in sig.items():
@@ -251,6 +252,13 @@ def ng_calibration_plan(n_conns: int, n_nodes: int, max_delay: int, sort_ranges:
     _check(lib().ng_calibration_plan(n_conns, n_nodes, max_delay, sort_ranges, out))
     keys = ("msd", "b1", "b2", "b3", "narrow_a", "narrow_b", "wgs_c", "tpr")
     return {k: int(v) for k, v in zip(keys, out)}
+
+
+def ng_calibration_form(n_conns: int, n_nodes: int, max_delay: int, sort_ranges: int = 1024) -> str:
+    """The form the default calibration takes, as a name of CALIBRATIONS: "msd" or "lsd"."""
+    form = ctypes.c_int32()
+    _check(lib().ng_calibration_form(n_conns, n_nodes, max_delay, sort_ranges, ctypes.byref(form)))
+    return {v: k for k, v in CALIBRATIONS.items()}[int(form.value)]
 
 
 def ng_create(cfg: ng_config, arena, arena_bytes: int, stream) -> ctypes.c_void_p:
