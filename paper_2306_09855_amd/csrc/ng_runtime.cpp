@@ -1252,17 +1252,17 @@ int calibrate_lsd(std::vector<CalSeg>& segs, const Uploader* upload, ScratchBump
 // its ng_read_timing reports; without arena room for the upload every context
 // does.
 int flush_connects_packed(ng_ctx* const* cs, uint32_t n) {
-  ng_ctx* c0 = cs[0];
   std::vector<ng_ctx*> with;
   uint64_t n_entries = 0, n_descs = 0;
   for (uint32_t i = 0; i < n; ++i)
-    if (!cs[i]->queued.empty() && cs[i]->stream == c0->stream && cs[i]->gen_quads == c0->gen_quads &&
+    if (!cs[i]->queued.empty() && cs[i]->stream == cs[0]->stream && cs[i]->gen_quads == cs[0]->gen_quads &&
         !timed_launch(cs[i], "generate_batch")) {
       with.push_back(cs[i]);
       n_entries += cs[i]->blocks.size() - cs[i]->tab_synced;
       n_descs += cs[i]->queued.size();
     }
   if (with.size() < 2) return NG_OK;
+  ng_ctx* c0 = with[0];  // its arena and staging hold the upload
   const uint64_t ebytes = align256(sizeof(ng::TabEntry) * n_entries), bytes = ebytes + sizeof(ng::GenDesc) * n_descs;
   char* d = ctx_alloc(c0, bytes);
   if (!d) return NG_OK;

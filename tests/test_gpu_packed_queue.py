@@ -37,7 +37,7 @@ def _check(net, wl):
     check_calibrated(net.fetch(), *net.group_index(), ref, wl.calls)
 
 
-@pytest.mark.parametrize("timed", [(0, 1, 2), (1,), (0, 2)])
+@pytest.mark.parametrize("timed", [(0, 1, 2), (0,), (1,), (0, 2)])
 def test_each_context_times_its_own_generation(timed):
     wls = _workloads(8, 1000, 3)
     nets = [_queued(wl) for wl in wls]
