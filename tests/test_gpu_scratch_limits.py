@@ -32,10 +32,11 @@ class _Built:
     """The workload's connections in an arena of `arena` bytes (None: ample),
     calibrated in `form`: arrays, index, kernels launched and arena bytes."""
 
-    def __init__(self, wl, form, block, arena=None, calibrate=ng.ng_calibrate):
+    def __init__(self, wl, form, block, arena=None, calibrate=ng.ng_calibrate, ranges=1024):
         ample = arena_bytes_for(wl.n_syn, wl.n_nodes, wl.max_delay, block) + 24 * wl.n_syn
         with Network(wl.seed, wl.h, block, arena or ample) as net:
             net.set_calibration(form)
+            net.tune(9, ranges)
             net.build(wl, calibrate=False)
             net.sync()
             self.before = net.memory_stats()[0]
@@ -91,6 +92,12 @@ def test_msd_form_in_its_bytes(n, nodes, delay):
     assert "downsweep" in lsd.kernels
     ample.same(lsd)
     tight.same(lsd)
+
+
+def test_msd_lists_that_the_counts_cannot_hold():
+    # one range: fewer of the first scatter's counts than list words
+    wl = _wl(3_000_000, 100, 3)
+    _Built(wl, "msd", 1 << 18, ranges=1).same(_Built(wl, "lsd", 1 << 18))
 
 
 def test_default_form_goes_on_without_room_for_msd():
