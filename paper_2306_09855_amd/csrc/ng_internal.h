@@ -124,9 +124,10 @@ uint32_t sort_tile_size(bool small);
 // has the CU to itself, at the price of shorter runs and more counts to scan.
 // Builds calibrated by large tiles, and by small ones: 374 and 315 us at 1e7
 // connections, 962 and 828 at 3e7, 1.87 and 1.59 ms at 6e7, 3.69 and 3.13 at
-// 1.2e8, 9.03 and 8.19 at 3e8 in 8-bit digits; but 15.9 and 16.7 at 4.3e8 in
-// 9-bit ones, whose counts take as many bytes as there are records.  (Two
-// small tiles per range: 302 us at 8e6, one 264.)
+// 1.2e8.  Above the line it depends on the digits, by which it does not
+// tell them apart: 9.03 and 8.19 ms at 3e8 in 8-bit ones, but 15.9 and 16.7 at
+// 4.3e8 in 9-bit ones, whose counts take as many bytes as there are records.
+// (Two small tiles per range: 302 us at 8e6, one 264.)
 inline bool sort_small_tiles(uint64_t records) { return records < (1ull << 27); }
 constexpr uint32_t kSmallRanges = 64;
 inline uint64_t sort_max_ranges(uint32_t sort_ranges, bool small) {

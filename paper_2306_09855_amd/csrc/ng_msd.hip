@@ -730,9 +730,9 @@ __global__ __launch_bounds__(256) void k_msd_split(MsdPlan p) {
   const uint32_t w = blockIdx.x * 256u + threadIdx.x;
   if (w < 2) p.big_count[w] = 0;  // sub-buckets and pieces listed by pass C
   if (w > p.wgs_c) return;
-  // the last boundary is the first sub-bucket past the records: the empty
-  // sub-buckets above it are never visited (their group counts and masks are
-  // zero from k_msd_zero)
+  // the last boundary is nsb_used: only the sub-buckets that no key below
+  // n_nodes << dbits reaches are never visited (their group counts and masks
+  // are zero from k_msd_zero); empty ones below it are walked in runs
   const uint64_t target = (uint64_t)w * (p.n + (uint64_t)p.nsb_used * p.sb_cost) / p.wgs_c;
   uint32_t lo = 0, hi = p.nsb_used;  // first sb with at least the target's work before it
   while (lo < hi) {

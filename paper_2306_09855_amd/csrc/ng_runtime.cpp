@@ -1117,15 +1117,21 @@ bool msd_geometry(uint64_t N, uint32_t nn, int dbits, int log2B, uint32_t sort_r
 }
 
 // The default radix calibration takes the most-significant-digit form when
-// (1) there are at least 2^24 connections: below, the LSD passes in small
-// tiles are faster (kernels of a build at 24 to 42 connections per possible
-// key, LSD against MSD: 0.30 and 0.34 ms at 9e6, 0.42 and 0.45 at 1.4e7, 0.58
-// and 0.59 at 2e7, 0.90 and 0.90 at 3.3e7, 1.21 and 1.13 at 4.5e7; whole
-// builds at 3e7 0.94 and 0.91); (2) the sub-buckets it must visit hold 256 connections on
-// average or more; and (3) there are at least 2.5 connections per possible
-// key (below, pass C sorts nearly empty tiles of 512 keys: 1.74 and 1.73 ms
-// at 2.8 per key and 5.4e7 uneven connections, 0.95 and 1.13 at 2.3 and
-// 2.9e7, 2.0 and 2.6 at 0.8 and 5.3e7; 14.4 and 11.0 at 6.9 and 4.4e8).
+// (1) there are at least 2^24 connections, (2) the sub-buckets it must visit
+// hold 256 connections on average or more, and (3) there are at least 2.5
+// connections per possible key (below, pass C sorts nearly empty tiles of 512
+// keys).  Calibrations of uniform connections with ng_sync, LSD against MSD in us:
+//   per key   1.7e7        2.5e7        3.3e7        4e7          5.5e7
+//   2.6       549   623    782   872    1037  1092   1264  1275   1766  1700
+//   5         530   517    748   765     962   956   1152  1078   1657  1467
+//   10        501   488    708   672     914   820   1091   906   1521  1382
+//   40        466   479    642   656     822   790    973   886   1342  1206
+// From 5 per key on the two are level (-3 to +5%) at 2^24 and the MSD form
+// gains from there; below 2^24 the LSD form in small tiles is ahead (kernels
+// at 24 to 42 per key: 0.30 and 0.34 ms at 9e6, 0.42 and 0.45 at 1.4e7).  The
+// line of 2.5 is drawn for large counts: near it MSD gains from about 4.5e7
+// connections on (14.4 and 11.0 ms at 6.9 per key and 4.4e8) and loses up to
+// 12% below; at 0.8 per key it loses at 5.3e7 too (2.0 and 2.6 ms).
 bool msd_pays(const ng::MsdPlan& p) {
   const uint64_t keyspace = (uint64_t)p.n_nodes << p.dbits;
   return p.n >= (1u << 24) && (uint64_t)p.n >= (256ull << (p.b1 + p.b2)) && (uint64_t)p.n * 2 >= keyspace * 5;
