@@ -13,14 +13,14 @@ __host__ __device__ inline uint32_t part_probe(uint32_t a, uint32_t b, uint32_t 
 }
 
 // [a, b] after a round: f = the first t whose key is at or past the sought one,
-// 8 if none is.  A search that has ended (a == b) stays as it is while another
-// one goes on.  It ends at the smallest key of [a, b) at or past the sought
+// 8 if none is.  A search that has ended (a == b: its trial keys are b, f is 0
+// or 8) stays as it is while another one goes on.  It ends at the smallest key of [a, b) at or past the sought
 // one, at the first b if there is none.
 __host__ __device__ inline void part_narrow(uint32_t& a, uint32_t& b, uint32_t f) {
-  if (a == b) return;
+  const bool open = a != b;
   const uint32_t na = f > 0 ? part_probe(a, b, f - 1) + 1 : a;
   if (f < 8) b = part_probe(a, b, f);
-  a = na;
+  if (open) a = na;
 }
 
 }  // namespace ng
