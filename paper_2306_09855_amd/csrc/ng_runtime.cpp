@@ -1040,16 +1040,17 @@ int calibrate_copass(ng_ctx* c) {
 // they fit one digit, else are split between A and B so that the occupied
 // values of D1 and the values of D2 balance (both set the run lengths of
 // their scatter).  False if the plan does not apply (the LSD sort runs).
+// fill = the records an average sub-bucket may hold (0: half an LDS load).
 bool msd_geometry(uint64_t N, uint32_t nn, int dbits, int log2B, uint32_t sort_ranges, ng::MsdPlan& p,
-                  uint32_t msd_tile = 0) {
+                  uint32_t msd_tile = 0, uint64_t fill = 0) {
   const int sbits = bitwidth(nn > 0 ? nn - 1 : 0);
   const int K = sbits + dbits;
   if (N == 0 || N > ng::kMsdMaxConns || K < 2 || K > (int)ng::kMsdMaxKeyBits) return false;
   const uint32_t tbits = (uint32_t)std::max(1, sbits);
   const uint64_t keyspace = (uint64_t)nn << dbits;
-  const uint64_t cap = ng::msd_cap(tbits + ng::kMsdMaxDigit <= 32);
+  if (!fill) fill = ng::msd_cap(tbits + ng::kMsdMaxDigit <= 32) / 2;
   int b3 = 0;
-  while (b3 < 9 && ((keyspace * (cap / 2)) >> (b3 + 1)) >= N) ++b3;
+  while (b3 < 9 && ((keyspace * fill) >> (b3 + 1)) >= N) ++b3;
   b3 = std::max(b3, std::max(1, K - 18));
   b3 = std::min(b3, std::min(9, K - 1));
   const int hb = K - b3;
@@ -1115,6 +1116,10 @@ bool msd_geometry(uint64_t N, uint32_t nn, int dbits, int log2B, uint32_t sort_r
   p.mask_words = std::max<uint32_t>(1, (1u << b3) / 32);
   return true;
 }
+
+// Average records of a sub-bucket in plans for arenas without room for the
+// usual ones (4,096 of packed records).
+constexpr uint64_t kMsdWideFill = 5120;
 
 // The default radix calibration takes the most-significant-digit form when
 // (1) there are at least 2^24 connections, (2) the sub-buckets it must visit
@@ -1367,9 +1372,19 @@ int calibrate_many(ng_ctx* const* cs, uint32_t n, const Uploader* upload, Scratc
     const CalSeg& g = segs[0];
     if (msd_geometry(g.N, g.nn, g.dbits, g.c->log2B, g.c->sort_ranges, mp, g.c->msd_tile) &&
         (g.c->calib_mode == NG_CALIB_RADIX_MSD || msd_pays(mp))) {
-      const int rc = calibrate_msd(segs[0], mp);
-      if (rc != NG_ERR_OOM || g.c->calib_mode == NG_CALIB_RADIX_MSD) return rc;
+      int rc = calibrate_msd(segs[0], mp);
+      if (rc != NG_ERR_OOM) return rc;
       msd_need = g.c->need;
+      // larger sub-buckets, where the last digit gets wider by them, halve the
+      // tables of the sub-buckets: the arena may have room for those
+      ng::MsdPlan wider;
+      if (msd_geometry(g.N, g.nn, g.dbits, g.c->log2B, g.c->sort_ranges, wider, g.c->msd_tile, kMsdWideFill) &&
+          wider.b3 > mp.b3) {
+        rc = calibrate_msd(segs[0], wider);
+        if (rc != NG_ERR_OOM) return rc;
+        msd_need = g.c->need = std::min(g.c->need, msd_need);
+      }
+      if (g.c->calib_mode == NG_CALIB_RADIX_MSD) return rc;
     }
   }
   // few records in all: small tiles, or large ones where the arena (or the

@@ -54,12 +54,14 @@ class _Built:
         assert np.array_equal(self.index[0], other.index[0]) and np.array_equal(self.index[1], other.index[1])
 
 
-def _msd_bytes(n, nodes, delay, block, ranges=1024):
+def _msd_bytes(n, nodes, delay, block, ranges=1024, digits=None):
     """The calibrated blocks, index and scratch of the most-significant-digit
     form: the records of each pass, a group slot per connection, the digit
     counts and tables, and a word per 10,241 connections for lists."""
     p = ng.ng_calibration_plan(n, nodes, delay, ranges)
     assert p["msd"] >= 1
+    if digits:
+        p["b1"], p["b2"], p["b3"] = digits
     rec_a, rec_b = (8 if p["narrow_a"] else 12), (8 if p["narrow_b"] else 12)
     nb, nsb = 1 << p["b1"], 1 << (p["b1"] + p["b2"])
     na = nb * -(-(-(-n // 10240)) // p["tpr"])
@@ -90,6 +92,28 @@ def test_msd_form_in_its_bytes(n, nodes, delay):
     tight = _Built(wl, "msd", block, ample.before + need)
     lsd = _Built(wl, "lsd", block)
     assert "downsweep" in lsd.kernels
+    ample.same(lsd)
+    tight.same(lsd)
+
+
+@pytest.mark.parametrize("n,nodes,delay,usual,wider", [
+    (1_840_000, 800, 1, (5, 5, 1), (9, 0, 2)),
+    (2_300_000, 16_000, 1, (5, 5, 5), (9, 0, 6)),
+    (4_312_500, 30_000, 7, (6, 5, 7), (5, 5, 8)),
+    (2_841_937, 19_770, 7, (6, 5, 7), (5, 5, 8)),
+])
+def test_msd_form_in_the_bytes_of_larger_sub_buckets(n, nodes, delay, usual, wider):
+    # sub-buckets of 4,096 to 5,120 records on average, of half as many usually
+    block = 1 << 18
+    wl = _wl(n, nodes, delay)
+    p = ng.ng_calibration_plan(n, nodes, delay)
+    assert (p["b1"], p["b2"], p["b3"]) == usual
+    need, least = (_msd_bytes(n, nodes, delay, block, digits=d) for d in (usual, wider))
+    assert least < need
+    ample = _Built(wl, "msd", block)
+    tight = _Built(wl, "msd", block, ample.before + least)
+    assert ample.peak - ample.before > least and tight.peak - tight.before <= least
+    lsd = _Built(wl, "lsd", block)
     ample.same(lsd)
     tight.same(lsd)
 
