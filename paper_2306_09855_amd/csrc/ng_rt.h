@@ -44,13 +44,16 @@ class Arena {
     free_.clear();
     if (size) free_[0] = size;
   }
-  char* alloc(uint64_t bytes) {
+  // First fit from the low end, or, for what is given back before the
+  // allocations made meanwhile (transient), from the high end, where it leaves
+  // no hole below them.
+  char* alloc(uint64_t bytes, bool transient = false) {
     std::lock_guard<std::mutex> lk(mu_);
     bytes = round_up(bytes ? bytes : 1);
-    char* p = first_fit_locked(bytes);
+    char* p = transient ? last_fit_locked(bytes) : first_fit_locked(bytes);
     if (!p && deferred_bytes_) {
       reclaim_locked();
-      p = first_fit_locked(bytes);
+      p = transient ? last_fit_locked(bytes) : first_fit_locked(bytes);
     }
     return p;
   }
@@ -87,6 +90,19 @@ class Arena {
         const uint64_t off = it->first, sz = it->second;
         free_.erase(it);
         if (sz > bytes) free_[off + bytes] = sz - bytes;
+        used_ += bytes;
+        peak_ = std::max(peak_, used_);
+        return base_ + off;
+      }
+    }
+    return nullptr;
+  }
+  char* last_fit_locked(uint64_t bytes) {
+    for (auto it = free_.rbegin(); it != free_.rend(); ++it) {
+      if (it->second >= bytes) {
+        const uint64_t off = it->first + it->second - bytes;
+        it->second -= bytes;
+        if (it->second == 0) free_.erase(it->first);
         used_ += bytes;
         peak_ = std::max(peak_, used_);
         return base_ + off;
@@ -256,7 +272,7 @@ struct ng_ctx {
 namespace ngrt {
 
 // Allocate from the context's arena, counting what the context holds.
-char* ctx_alloc(ng_ctx* c, uint64_t bytes);
+char* ctx_alloc(ng_ctx* c, uint64_t bytes, bool transient = false);
 
 // A set of context allocations made all-or-nothing.
 struct AllocSet {

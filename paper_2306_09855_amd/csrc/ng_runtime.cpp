@@ -365,8 +365,8 @@ void ctx_host_release(ng_ctx* c) {
   c->ev_pool.clear();
 }
 
-char* ctx_alloc(ng_ctx* c, uint64_t bytes) {
-  char* p = c->arena->alloc(bytes);
+char* ctx_alloc(ng_ctx* c, uint64_t bytes, bool transient) {
+  char* p = c->arena->alloc(bytes, transient);
   if (p) c->held += Arena::round_up(bytes ? bytes : 1);
   return p;
 }
@@ -1819,7 +1819,9 @@ static int connect_pairwise(ng_ctx* c, ng_range src, ng_range tgt, const ng_conn
     if (!host_words(c, 1)) return NG_ERR_DEVICE;
     cbytes = 4 * (units + 1);
     const uint64_t tbytes = 4 * ng::scan_tmp_words(units);
-    counts = (uint32_t*)ctx_alloc(c, cbytes + tbytes);
+    // from the arena's high end: the call's blocks come below, where these
+    // would leave a hole that the next calibration's arrays may not fit
+    counts = (uint32_t*)ctx_alloc(c, cbytes + tbytes, true);
     if (!counts) {
       c->need = Arena::round_up(cbytes + tbytes);
       return fail(NG_ERR_OOM, "arena cannot hold the pair counts");
@@ -1829,7 +1831,7 @@ static int connect_pairwise(ng_ctx* c, ng_range src, ng_range tgt, const ng_conn
     // the decisions of the counting pass, kept for the writing pass when the
     // arena has room (one bit per pair), else evaluated again
     bits_bytes = units * (ng::kPbUnit / 8);
-    bits = (uint64_t*)ctx_alloc(c, bits_bytes);
+    bits = (uint64_t*)ctx_alloc(c, bits_bytes, true);
     if (!bits) bits_bytes = 0;
     NG_LAUNCH(c, "pb_count", ng::launch_pb_count(d, key_ptr(c), counts, bits, c->stream));
     NG_LAUNCH(c, "scan", ng::launch_exclusive_scan(counts, counts, units, tmp, counts + units, c->stream));

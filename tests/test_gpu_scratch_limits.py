@@ -216,3 +216,28 @@ def test_copass_in_its_bytes(n, nodes, delay, block):
     lsd = _Built(wl, "lsd", block)
     ample.same(lsd)
     tight.same(lsd)
+
+
+@pytest.mark.parametrize("ns,nt", [(1500, 2000), (60_000, 50)])
+def test_pairwise_leaves_no_hole_in_the_arena(ns, nt):
+    # the counts and decisions of the call are gone before the calibration,
+    # which fits in just its bytes above the call's blocks
+    nodes, delay, block, p = 60_000, 30, 1 << 16, 0.05
+    syn = ng.syn_spec(("normal", 0.5, 0.05), ("uniform_int", 1, delay))
+
+    def build(arena):
+        with Network(5, 0.1, block, arena) as net:
+            net.set_calibration("lsd")
+            net.create(nodes)
+            _, _, n = ng.ng_connect(net.ctx, ng.ng_range(0, ns), ng.ng_range(0, nt),
+                                    ng.conn_spec("pairwise_bernoulli", 0, p=p), syn)
+            before = net.memory_stats()[0]
+            net.calibrate()
+            return n, before, net.fetch(), net.group_index()
+
+    n, before, out, index = build(64 << 20)
+    tight = build(before + sum(_lsd_bytes(n, nodes, delay, block, False)))
+    assert tight[0] == n
+    for k in out:
+        assert np.array_equal(out[k].view(np.uint8), tight[2][k].view(np.uint8)), k
+    assert np.array_equal(index[0], tight[3][0]) and np.array_equal(index[1], tight[3][1])
